@@ -262,6 +262,32 @@ def test_arrays_edges(gpu):
     assert e.value.status == gpu.EMISMATCH
 
 
+@pytest.mark.parametrize("shape,depth", [("x_line", 12), ("y_line", 12), ("z_line", 12), ("plane", 9),
+                                         ("two_sheets", 10), ("sparse", 21), ("one_x", 6)])
+def test_arrays_nn_outward(gpu, shape, depth):
+    """The outward walk where one side, one run or one level holds everything."""
+    rng = np.random.default_rng(74)
+    side = 1 << depth
+    p = rng.integers(0, side, (700, 3)).astype(np.float32)
+    if shape.endswith("_line"):
+        keep = "xyz".index(shape[0])
+        p[:, [a for a in range(3) if a != keep]] = side // 3
+    elif shape == "plane":
+        p[:, 0] = np.floor((p[:, 1] + p[:, 2]) / 2)
+    elif shape == "two_sheets":
+        p[:, 2] = np.where(p[:, 2] < side // 2, 3, side - 4)
+    elif shape == "one_x":
+        p[:, 0] = 17
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, L)
+    k, arr, _ = _lin_arrays(gpu, p, g)
+    q = np.concatenate([p[:60] + 1, rng.integers(-5, side + 5, (200, 3)),
+                        [[0, 0, 0], [side - 1] * 3, [side // 2] * 3]]).astype(np.float32)
+    idx, d2 = gpu.cga_arrays_nn(arr, dev(q), g)
+    widx, wd2 = oracle.knn_brute(u64(k), q, g, 1)
+    np.testing.assert_array_equal(d2.cpu().numpy().view(np.uint64), wd2[:, 0])
+    np.testing.assert_array_equal(idx.cpu().numpy(), widx[:, 0])
+
+
 # ------------------------------------------------------------------- merge
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s", "w_c3s"])
 @pytest.mark.parametrize("mode", [M, L])
