@@ -1062,14 +1062,15 @@ def main():
     # counter run of the same kernel sources
     work = knn_work(cga, pipe)
     progress(f"k-NN work per query: {work}")
-    # a node visit reads the node's two words (mask and first child; oriented box)
-    knn_bytes_q = 12 + 16 * pipe.k + 16 * work["node_loads"] + 4 * work["dense_loads"]
+    # a node's record is 32 bytes (its two boxes), a leaf's voxel 8
+    knn_bytes_q = 12 + 16 * pipe.k + 32 * work["node_loads"] + 8 * work["dense_loads"]
     knn = {"queries": nq, "k": pipe.k, "stage_ms": round(st[2], 4),
            "queries_per_s": nq / (st[2] * 1e-3),
            "work_per_query": {k: round(v, 2) for k, v in work.items()},
            "bytes_per_query": {"algorithmic": round(knn_bytes_q, 1),
-                               "every_node_load_a_line": round(12 + 16 * pipe.k + 128 * (
-                                   work["node_loads"] + work["dense_loads"]), 1)}}
+                               # 16 records are 512 bytes, a leaf 128
+                               "every_node_load_a_line": round(12 + 16 * pipe.k + 8 * (
+                                   4 * work["node_loads"] + work["dense_loads"]), 1)}}
     if knn_prof[1]:
         avg_ms = knn_prof[0] / knn_prof[1]
         achieved = nq * knn_bytes_q / (avg_ms * 1e-3) / 1e9

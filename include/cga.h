@@ -262,10 +262,9 @@ int cga_project(const cga_grid *grid, const void *d_keys, int64_t n, const int64
  * the workspace then grows by about 24 bytes per query, so size it with the
  * same nq as the call).  Launch knobs, read from the environment at each
  * call, change no result: CGA_KNN_ORDER (1 / 0: the Morton ordering on /
- * off), CGA_KNN_LA (level of the first round's cell, default 4),
- * CGA_KNN_QUEUE (1 / 0: teams take queries from a counter / round-robin;
- * by default the counter from 8 queries per resident team) and
- * CGA_KNN_BLOCKS (a cap on the search's grid).
+ * off), CGA_KNN_QUEUE (1 / 0: teams take queries from one counter / from
+ * their block's; by default the one counter from 8 queries per resident
+ * team) and CGA_KNN_BLOCKS (a cap on the search's grid).
  * Errors: CGA_ENONFINITE for a non-finite query (device); CGA_EMISMATCH
  * (device) when the keys are not sorted, unique and within the grid (the
  * results are then unspecified, but every access stays in bounds). */
@@ -275,10 +274,11 @@ int cga_knn(const cga_grid *grid, const void *d_keys, int64_t n, const int64_t *
             size_t ws_bytes, cga_stream stream);
 /* The same search built with work counters, for measurement: identical
  * outputs, and d_work (device, 4 uint64, accumulated -- the caller zeroes
- * it) gains the search's node-record loads (16 B each), dense-table loads (4 B
- * each), voxels offered to the candidate list and walk-loop steps, summed
- * over all queries and lanes.  The search is deterministic, so these are the
- * exact per-call work of cga_knn on the same input. */
+ * it) gains the search's node-record loads (32 B each), the voxels it read
+ * from the dense runs of the leaves (8 B each), the voxels offered to the
+ * candidate list and the nodes and leaves entered, summed over all queries.
+ * The search is deterministic, so these are the exact per-call work of
+ * cga_knn on the same input. */
 int cga_knn_count(const cga_grid *grid, const void *d_keys, int64_t n, const int64_t *d_n,
                   const float *d_q, int64_t nq, int k, int64_t *d_idx, uint64_t *d_d2,
                   uint64_t *d_work, void *d_ws, size_t ws_bytes, cga_stream stream);

@@ -452,7 +452,8 @@ def cga_knn_count(keys: torch.Tensor, queries: torch.Tensor, grid, k: int, *, n=
                   idx_out=None, d2_out=None, ws=None, stream=None):
     """cga_knn built with work counters: (indices, squared distances, work)
     where work = {node_loads, dense_loads, voxels_offered, steps}, totals
-    over all queries (synchronises)."""
+    over all queries: node records and leaf voxels read, voxels offered to
+    the list, nodes and leaves entered (synchronises)."""
     n = keys.shape[0] if n is None else int(n)
     nq = queries.shape[0]
     g = grid_struct(grid)

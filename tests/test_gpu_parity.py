@@ -736,6 +736,34 @@ def test_knn_linear(gpu, w_c1, w_c2s, monkeypatch, ordered):
     _check_knn(gpu, k21, rng.uniform(0, 1, (700, 3)).astype(np.float32), g21, 4)
 
 
+@pytest.mark.parametrize("depth", [11, 15, 16])  # 64-bit keys; packed and wide lists
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 255, 256, 257, 4095, 4097, 65536, 65537, 70001])
+def test_knn_hierarchy_sizes(gpu, n, depth):
+    """Key counts at the edges of the hierarchy's leaves, nodes, tiles and
+    levels; queries on, beside and far from the voxels; lists that fill no
+    lane, some, one each and two each; the count on the device below the
+    bound."""
+    import torch
+    rng = np.random.default_rng(n + depth)
+    side = 1 << depth
+    u = rng.integers(0, side, (2 * n + 64, 2))
+    p = np.stack([u[:, 0], u[:, 1], (u[:, 0] // 3 + 2 * u[:, 1] // 5) % side], 1)  # a folded sheet
+    keys = np.unique(oracle.encode(p, depth, M))
+    keys = np.sort(rng.permutation(keys)[:n])
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, M)
+    q = np.concatenate([p[:20], p[:20] + rng.integers(-3, 4, (20, 3)),
+                        rng.integers(-9, side + 9, (20, 3))]).astype(np.float32)
+    kd = dev(keys.view(np.int64) if 3 * depth > 32 else keys.astype(np.uint32).view(np.int32))
+    for k in (1, 5, 16, 17, 32):
+        _check_knn(gpu, kd, q, g, k, tier="brute")
+    short = max(n - 16, 1)
+    d_n = torch.tensor([short], dtype=torch.int64, device=kd.device)
+    idx, d2 = gpu.cga_knn(kd, dev(q), g, 9, d_n=d_n)
+    widx, wd2 = oracle.knn_brute(keys[:short], q, g, 9)
+    np.testing.assert_array_equal(idx.cpu().numpy(), widx)
+    np.testing.assert_array_equal(d2.cpu().numpy().view(np.uint64), wd2)
+
+
 # ------------------------------------------------------------------ lookup
 def test_binary_lookup(gpu):
     rng = np.random.default_rng(33)
