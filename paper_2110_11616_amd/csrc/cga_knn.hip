@@ -50,9 +50,21 @@ constexpr uint32_t kPackedDepth = 15;              // deepest grid with 32-bit s
 constexpr int kOrderBits = 24;
 constexpr int64_t kOrderMin = (int64_t)1 << 18;
 constexpr int kLinearSortCtr = 8;  // tile counters of the LINEAR keys' re-key sort (up to 8 passes)
-constexpr int kKnnQueryCtr = 20;   // control-block counter of the search's query queue
+// Query counters of the search: group g of G of the blocks (blockIdx mod G)
+// answers queries g, g + G, ... from its own counter, a cache line apart.
+// Atomics on one word take about 10 ns each, so one counter for all teams set
+// the time of near queries (400k beside a LiDAR surface, k = 8: 3.9 ms, 1.1
+// with the groups' counters, 1.3 with a counter per block, whose work differs
+// too much).
+constexpr int kQueryGroups = 32;
+constexpr int kQueryCtrStride = 32;  // words
+// Groups of a grid: at least eight blocks each, so that one block more or
+// less in a group hardly unbalances them.
+__device__ __forceinline__ uint32_t query_groups(uint32_t blocks) {
+    const uint32_t g = blocks / 8;
+    return g < 1 ? 1 : (g < kQueryGroups ? g : kQueryGroups);
+}
 constexpr int kLeafTrips = 4;      // leaves a team may visit per trip of the search loop
-constexpr int64_t kKnnQueuePerTeam = 8;  // queries per team from which the search uses it
 
 template <typename K>
 __device__ __forceinline__ int64_t lower_bound_dev(const K *keys, int64_t n, K q) {
@@ -468,14 +480,17 @@ __global__ __launch_bounds__(256) void k_bvh_low(const K *__restrict__ keys, int
                                                  const int64_t *d_n, uint32_t depth, BvhShape S,
                                                  uint64_t *__restrict__ vox,
                                                  uint64_t *__restrict__ rec,
-                                                 float *__restrict__ mom, uint32_t *err) {
+                                                 float *__restrict__ mom,
+                                                 uint32_t *__restrict__ qctr, uint32_t *err) {
     constexpr int kStride = kTeam + 1;  // LDS words per leaf, off by one against bank conflicts
     __shared__ uint64_t s_v[256 * kStride];
     __shared__ uint32_t s_u[16];
     __shared__ float s_f[16];
     const int64_t n = key_count(n_host, d_n), base = (int64_t)blockIdx.x * kBvhTile;
-    if (base >= n) return;  // block-uniform
     const int tid = threadIdx.x;
+    if (blockIdx.x == 0)  // the search's query counters start at zero
+        for (int i = tid; i < kQueryGroups * kQueryCtrStride; i += 256) qctr[i] = 0;
+    if (base >= n) return;  // block-uniform
     bool bad = false;
 #pragma unroll 4
     for (int r = 0; r < kBvhTile / 256; ++r) {
@@ -874,8 +889,8 @@ struct WideList {
 };
 
 // One query at a time per team of 16 lanes: each team's first query by its
-// place in the grid, the next ones from a counter: the call's (qctr, zero at
-// launch) or, without it, the block's own in LDS over every grid-stride'th
+// place in the grid, the next ones from a counter: its group's (qctr, zero at
+// launch) or, without them, the block's own in LDS over every grid-stride'th
 // run of 16 queries.  LIST is PackedList (depth <= 15) or
 // WideList; KT (16 or 32) its capacity.  The kernel is one loop whose every
 // trip moves each team one step in its own query.  kCount (a measurement
@@ -908,11 +923,19 @@ __global__ __launch_bounds__(kKnnBlock) void k_knn_bvh(
     constexpr uint32_t kInf = 0x7F800000u;
 
     // ---- per query
-    int64_t slot = (int64_t)blockIdx.x * kTeamsPerBlock + team, j = 0;
+    // group g's blocks are g, g + G, ...: their teams' first queries are the
+    // group's first, and its counter goes on after them
+    const uint32_t groups = qctr ? query_groups(gridDim.x) : 1;
+    const uint32_t grp = blockIdx.x % groups;
+    const int64_t ahead = (int64_t)((gridDim.x - grp + groups - 1) / groups) * kTeamsPerBlock;
+    int64_t slot = qctr ? grp + (int64_t)groups * ((int64_t)(blockIdx.x / groups) * kTeamsPerBlock + team)
+                        : (int64_t)blockIdx.x * kTeamsPerBlock + team;
+    int64_t j = 0;
+    if (qctr) qctr += grp * kQueryCtrStride;
     uint32_t nxt = 0;  // lane 0: the team's next query from the counter, taken one query ahead
     auto next_slot = [&]() __attribute__((always_inline)) -> int64_t {
         const int64_t i = (int64_t)(uint32_t)__shfl((int)nxt, tbase, 64);
-        return qctr ? stride + i
+        return qctr ? grp + groups * (ahead + i)
                     : (int64_t)blockIdx.x * kTeamsPerBlock + (i & (kTeamsPerBlock - 1)) + (i / kTeamsPerBlock + 1) * stride;
     };
     Vox qv{0, 0, 0};
@@ -1134,12 +1157,11 @@ static bool knn_order(int64_t nq) {
     return nq >= kOrderMin;
 }
 
-// Launch knob (never changes results): CGA_KNN_QUEUE = 1 / 0 forces the
-// search's query counter on / off; by default it is on from
-// kKnnQueuePerTeam queries per resident team.
+// Launch knob (never changes results): CGA_KNN_QUEUE = 0 takes the search's
+// queries from counters of the blocks instead of the groups'.
 static int knn_queue_knob() {
     if (const char *e = getenv("CGA_KNN_QUEUE")) return atoi(e) != 0 ? 1 : 0;
-    return -1;
+    return 1;
 }
 
 // Launch knob (never changes results): CGA_KNN_BLOCKS = n caps the search's
@@ -1163,6 +1185,7 @@ struct KnnLayout {
     uint64_t *vox;  // the keys' voxels
     uint64_t *rec;  // node records, four words each
     float *mom;     // sums of the nodes from level 2 on, ten floats each (build only)
+    uint32_t *qctr; // the search's query counters
     size_t bytes;
 };
 
@@ -1193,6 +1216,7 @@ static KnnLayout knn_layout(void *ws, int64_t n, uint32_t depth, int64_t nq_orde
     L.vox = c.take<uint64_t>(m);
     L.rec = c.take<uint64_t>(4 * (size_t)L.shape.records);
     L.mom = c.take<float>(L.shape.top >= 3 ? 10 * (size_t)(L.shape.records - L.shape.off[2]) : 1);
+    L.qctr = c.take<uint32_t>(kQueryGroups * kQueryCtrStride);
     L.bytes = c.size();
     return L;
 }
@@ -1203,7 +1227,7 @@ static void bvh_build(const KnnLayout &L, const K *keys, int64_t n, const int64_
     CGA_PROF("knn_tree", s);
     const int64_t blocks = n > 0 ? (n + kBvhTile - 1) / kBvhTile : 1;
     k_bvh_low<K><<<(unsigned)blocks, 256, 0, s>>>(keys, n, d_n, depth, L.shape, L.vox, L.rec, L.mom,
-                                                  &L.ctl->err);
+                                                  L.qctr, &L.ctl->err);
     if (L.shape.top >= 3)
         k_bvh_high<<<1, kBvhHighBlock, 0, s>>>(n, d_n, L.shape, L.rec, L.mom);
 }
@@ -1248,15 +1272,9 @@ static void knn_launch(const cga_grid *g, const KnnLayout &L, int64_t n, const i
     int64_t cap = knn_resident_blocks<KT>(g->depth <= kPackedDepth, kCount);
     if (const int b = knn_blocks_knob(); b > 0 && b < cap) cap = b;
     const unsigned blocks = (unsigned)(want < cap ? want : cap);
-    // Teams take their queries from a counter (zeroed with the control block
-    // at the call's start) when each has many to take: a slow query then
-    // holds up only its own team.  With few queries per team the counter's
-    // atomics would contend, and the teams of a block share their block's.
-    // The counter's 32 bits must not wrap.
-    const int64_t teams = (int64_t)blocks * kTeamsPerBlock;
-    const int knob = knn_queue_knob();
-    const bool queue = knob >= 0 ? knob == 1 : nq >= kKnnQueuePerTeam * teams;
-    uint32_t *qctr = queue && nq < (int64_t)UINT32_MAX - teams ? &L.ctl->tile_ctr[kKnnQueryCtr] : nullptr;
+    // Teams take their queries from their group's counter, so that a slow
+    // query holds up only its own team.  The counters' 32 bits must not wrap.
+    uint32_t *qctr = knn_queue_knob() != 0 && nq < (int64_t)1 << 31 ? L.qctr : nullptr;
     if (g->depth <= kPackedDepth)
         k_knn_bvh<KT, PackedList<KT>, kCount><<<blocks, kKnnBlock, 0, s>>>(
             L.rec, L.vox, L.shape, n, d_n, q, nq, L.ob, g->origin[0], g->origin[1], g->origin[2],
