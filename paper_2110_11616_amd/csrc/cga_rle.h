@@ -49,8 +49,9 @@ __global__ __launch_bounds__(kRleBlock) void k_rle(const K *__restrict__ in, int
     __shared__ int32_t s_pl;
 
     const int tid = threadIdx.x;
-    const uint32_t tile = next_tile(tile_ctr, &s_tile);
     const int64_t n = dev_count(n_host, d_n);
+    if (n <= 0) return;  // no keys: leave before the tile counter, whose adds take turns
+    const uint32_t tile = next_tile(tile_ctr, &s_tile);
     const int64_t base = (int64_t)tile * kRleTile;
     if (base >= n) return;
 

@@ -180,6 +180,10 @@ __global__ __launch_bounds__(kSortBlock) void k_onesweep(
     __shared__ K s_keys[TILE];
     __shared__ V s_vals[kHasVal ? TILE : 1];
 
+    // no keys at all (a count left at zero by the launch before): leave before
+    // the tile counter, whose adds take turns
+    const int64_t n_all = SEG ? 0 : dev_count(n_host, d_n);
+    if (!SEG && n_all <= 0) return;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     for (int i = tid; i < WAVES * RADIX; i += BLOCK) (&s_wcnt[0][0])[i] = 0;
     const uint32_t tile = next_tile(tile_ctr, &s_tile);
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(kSortBlock) void k_onesweep(
         n = seg_off[lo + 1];
         digit_base += (size_t)lo * RADIX;
     } else {
-        n = dev_count(n_host, d_n);
+        n = n_all;
         base = (int64_t)tile * TILE;
         if (base >= n) return;  // uniform across the block
     }

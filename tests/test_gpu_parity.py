@@ -349,6 +349,71 @@ def test_project_depth_limits(gpu):
                 assert np.array_equal(u64(p), wp) and np.array_equal(u32(c), wc)
 
 
+def _project_both(gpu, kd, g, axis, want, counts):
+    """The waiting call, the call that leaves its size on the device, and the
+    sort (which a named setting selects) all give the wanted pixels."""
+    import torch
+    p, c = gpu.cga_project(kd, g, axis)
+    assert np.array_equal(u64(p), want) and np.array_equal(c.cpu().numpy(), counts)
+    z = torch.zeros(1, dtype=torch.int64, device=kd.device)
+    p, c, _ = gpu.cga_project(kd, g, axis, d_n_out=z, sync=False)
+    u = int(z)
+    assert np.array_equal(u64(p[:u]), want) and np.array_equal(c[:u].cpu().numpy(), counts)
+    p, c = gpu.cga_project(kd, g, axis, tune=(8, 16))
+    assert np.array_equal(u64(p), want) and np.array_equal(c.cpu().numpy(), counts)
+
+
+def _key_tensor(keys, depth):
+    return dev(keys.view(np.int64) if 3 * depth > 32 else keys.astype(np.uint32).view(np.int32))
+
+
+@pytest.mark.parametrize("depth", [1, 3, 4, 5, 10, 11, 12, 13, 14, 15])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_project_tiles(gpu, depth, axis):
+    """MORTON projections by tiles (up to depth 14) against the definition and
+    the sort: one key to many, repeated keys (counted each time), keys in no
+    order, and counts that stay on the device."""
+    rng = np.random.default_rng(100 * depth + axis)
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, M)
+    for n in (1, 2, 63, 65, 1025, 60_000):
+        keys = np.unique(rng.integers(0, 1 << (3 * depth), n, dtype=np.uint64))
+        forms = [keys]
+        if n == 1025:
+            forms += [np.sort(keys[rng.integers(0, len(keys), n)]), rng.permutation(keys)]
+        for ks in forms:
+            v = oracle.decode(ks, depth, M)
+            uv = np.delete(v, axis, 1)
+            want, counts = np.unique(oracle.encode2(uv[:, 0], uv[:, 1], depth, M), return_counts=True)
+            _project_both(gpu, _key_tensor(ks, depth), g, axis, want, counts)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 65_535, 65_536, 200_000, 262_144, 262_145])
+def test_project_tile_totals(gpu, n):
+    """One tile's voxels around the limits of its ways to count them (bitmap,
+    16-bit counters, the most that a tile takes), a pixel of more voxels than
+    its counter holds, and an output one pixel too small."""
+    rng = np.random.default_rng(n)
+    depth = 14
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, M)
+    ij = rng.permutation(128 * 128 * 64)[:n]
+    v = np.stack([1280 + ij % 128, 256 + ij // 128 % 128, ij // (128 * 128) * 37], 1)
+    keys = np.sort(oracle.encode(v, depth, M))
+    want, counts = np.unique(oracle.encode2(v[:, 0], v[:, 1], depth, M), return_counts=True)
+    kd = _key_tensor(keys, depth)
+    _project_both(gpu, kd, g, 2, want, counts)
+    with pytest.raises(gpu.CgaError) as e:
+        gpu.cga_project(kd, g, 2, cap=len(want) - 1)
+    assert e.value.status == gpu.ECAPACITY
+    if n == 65_536:
+        for reps in (65_535, 65_536, 70_000):
+            ks = np.sort(np.concatenate([keys, np.repeat(keys[777], reps - 1)]))
+            at = np.searchsorted(want, oracle.encode2(*oracle.decode(keys[777:778], depth, M)[0, :2, None],
+                                                      depth, M)[0])
+            more = counts.copy()
+            more[at] += reps - 1
+            _project_both(gpu, _key_tensor(ks, depth), g, 2, want, more)
+
+
 # --------------------------------------------------------------------- kNN
 def _check_knn(gpu, keys_gpu, q, g, k, tier="kd"):
     idx, d2 = gpu.cga_knn(keys_gpu, dev(q), g, k)
