@@ -532,7 +532,7 @@ def cga_occupancy(keys: torch.Tensor, grid, *, n=None, d_n=None, occ_out=None, c
                              _ptr(counts), _ptr(wsb), wsb.numel(), _stream(stream)), "cga_occupancy")
     if sync:
         _check(lib.cga_ws_status(_ptr(wsb), _stream(stream)), "cga_occupancy")
-        total = int(counts[1:].sum().item())
+        total = sum(counts[1:].tolist())
         return occ[:total], counts
     return occ, counts
 

@@ -67,11 +67,27 @@ int finish_sync(const Control *ctl, hipStream_t s) {
     return status_from_bits(bits);
 }
 
-// Host copy of a device count, after the stream has drained.
-static int read_count(const int64_t *d, int64_t *h, hipStream_t s) {
-    CGA_HIP(hipMemcpyAsync(h, d, sizeof *h, hipMemcpyDeviceToHost, s));
+int finish_counts(const Control *ctl, hipStream_t s, const int64_t *d0, int64_t *h0,
+                  const int64_t *d1, int64_t *h1, uint32_t *bits) {
+    // error bits and both counts lie at the block's start: each copy to the
+    // host is a round trip of about 15 us, so a call makes one
+    struct {
+        uint32_t err, pad;
+        int64_t count, count2;
+    } head;
+    static_assert(offsetof(Control, count) == 8 && offsetof(Control, count2) == 16, "control block");
+    CGA_HIP(hipMemcpyAsync(&head, ctl, sizeof head, hipMemcpyDeviceToHost, s));
+    const int64_t *d[2] = {d0, d1};
+    int64_t *h[2] = {h0, h1};
+    for (int i = 0; i < 2; ++i)
+        if (h[i] && d[i] != &ctl->count && d[i] != &ctl->count2)
+            CGA_HIP(hipMemcpyAsync(h[i], d[i], sizeof(int64_t), hipMemcpyDeviceToHost, s));
     CGA_HIP(hipStreamSynchronize(s));
-    return CGA_OK;
+    for (int i = 0; i < 2; ++i)
+        if (h[i] && (d[i] == &ctl->count || d[i] == &ctl->count2))
+            *h[i] = d[i] == &ctl->count ? head.count : head.count2;
+    if (bits) *bits = head.err;
+    return status_from_bits(head.err);
 }
 
 // Default tuning; the autotuner cache may override it per (key width, key
@@ -280,12 +296,7 @@ int cga_build(const cga_grid *g, const float *d_xyz, int64_t n, void *d_keys, ui
             build_enqueue<uint32_t>(g, d_xyz, n, (uint32_t *)d_keys, d_counts, cap, cnt_out, L, s);
         CGA_HIP(hipGetLastError());
     }
-    if (n_out_host) {
-        int st = finish_sync(L.ctl, s);
-        CGA_TRY(read_count(cnt_out, n_out_host, s));
-        return st;
-    }
-    return CGA_OK;
+    return n_out_host ? finish_counts(L.ctl, s, cnt_out, n_out_host) : CGA_OK;
 }
 
 int cga_encode_keys(const cga_grid *g, const float *d_xyz, int64_t n, void *d_keys, void *d_ws,
@@ -402,12 +413,7 @@ int cga_to_arrays(const cga_grid *g, const void *d_keys, int64_t n, const int64_
                                      d_y_index, d_y_ptr, d_z_index, nx, nxy, L, s);
         CGA_HIP(hipGetLastError());
     }
-    if (n_x_host || n_xy_host) {
-        int st = finish_sync(L.ctl, s);
-        if (n_x_host) CGA_TRY(read_count(nx, n_x_host, s));
-        if (n_xy_host) CGA_TRY(read_count(nxy, n_xy_host, s));
-        return st;
-    }
+    if (n_x_host || n_xy_host) return finish_counts(L.ctl, s, nx, n_x_host, nxy, n_xy_host);
     return CGA_OK;
 }
 

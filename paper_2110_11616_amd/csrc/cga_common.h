@@ -71,6 +71,11 @@ int launch_begin(Control *ctl, void *z0, size_t z0_bytes, void *z1, size_t z1_by
                  int64_t *zero3 = nullptr, int64_t *zero4 = nullptr);
 // Synchronise and translate the control block's error bits.
 int finish_sync(const Control *ctl, hipStream_t s);
+// The same, and the host copies of up to two device counts, with one wait:
+// counts in the control block come with the error bits in one copy.  *bits
+// (nullable) gets the error bits as they are.
+int finish_counts(const Control *ctl, hipStream_t s, const int64_t *d0, int64_t *h0,
+                  const int64_t *d1 = nullptr, int64_t *h1 = nullptr, uint32_t *bits = nullptr);
 
 // Optional per-kernel timing.  When enabled (cga_prof_enable), a launch
 // whose label matches the filter is bracketed by HIP events recorded on the

@@ -96,13 +96,7 @@ static int merge_call(const cga_grid *g, const void *d_a, int64_t na, const int6
                                     (uint32_t *)d_out, d_src, cap, cnt_out, L, s);
         CGA_HIP(hipGetLastError());
     }
-    if (n_out_host) {
-        int st = finish_sync(L.ctl, s);
-        CGA_HIP(hipMemcpyAsync(n_out_host, cnt_out, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        CGA_HIP(hipStreamSynchronize(s));
-        return st;
-    }
-    return CGA_OK;
+    return n_out_host ? finish_counts(L.ctl, s, cnt_out, n_out_host) : CGA_OK;
 }
 
 static bool merge_args_valid(const cga_grid *g, const void *d_a, int64_t na, const void *d_b,

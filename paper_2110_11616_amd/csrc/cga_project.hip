@@ -626,10 +626,8 @@ int cga_project(const cga_grid *g, const void *d_keys, int64_t n, const int64_t 
                                             (uint32_t *)d_out2d, d_counts, cap, cnt_out, L, s);
         if (n_out_host) {  // the caller waits anyway: look whether the tiles did it
             uint32_t bits = 0;
-            CGA_HIP(hipMemcpyAsync(&bits, &L.ctl->err, sizeof bits, hipMemcpyDeviceToHost, s));
-            CGA_HIP(hipMemcpyAsync(n_out_host, cnt_out, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            CGA_HIP(hipStreamSynchronize(s));
-            if (!(bits & kProjRedo)) return status_from_bits(bits);
+            const int st = finish_counts(L.ctl, s, cnt_out, n_out_host, nullptr, nullptr, &bits);
+            if (st == CGA_EHIP || !(bits & kProjRedo)) return st;
         } else {
             const size_t z0 = (sort_zero_bytes(L.sort) + 15) / 16, z1 = ((size_t)rle_tiles(n) * 8 + 15) / 16;
             const unsigned blocks = (unsigned)(z0 / 256 < 1 ? 1 : (z0 / 256 > 1024 ? 1024 : z0 / 256));
@@ -646,13 +644,7 @@ int cga_project(const cga_grid *g, const void *d_keys, int64_t n, const int64_t 
         sort_way(d_n);
         CGA_HIP(hipGetLastError());
     }
-    if (n_out_host) {
-        int st = finish_sync(L.ctl, s);
-        CGA_HIP(hipMemcpyAsync(n_out_host, cnt_out, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        CGA_HIP(hipStreamSynchronize(s));
-        return st;
-    }
-    return CGA_OK;
+    return n_out_host ? finish_counts(L.ctl, s, cnt_out, n_out_host) : CGA_OK;
 }
 
 }  // extern "C"
