@@ -435,9 +435,8 @@ static int batch_enqueue(const BatchArgs &a, hipStream_t s) {
         // unique composite keys go to the buffer the sort did not end in
         {
             CGA_PROF("rle", s);
-            k_rle<uint64_t, uint64_t, false><<<(unsigned)rle_tiles(n), kRleBlock, 0, s>>>(
-                fin, n, nullptr, 0, ~0ull, other, a.counts, nullptr, n, d_u, L.rle_status,
-                &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err);
+            rle_launch<uint64_t, uint64_t, false>(fin, n, nullptr, 0, ~0ull, other, a.counts, nullptr, n, d_u, L.rle_status,
+                &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err, s);
         }
         {
             CGA_PROF("batch_offsets", s);

@@ -163,9 +163,8 @@ static void build_enqueue(const cga_grid *g, const float *xyz, int64_t n, K *key
     encode_dispatch<K>(g, xyz, n, a, w.radix_bits, w.passes, w.hist, &L.ctl->err, s);
     K *fin = sort_chain<K>(w, a, b, n, nullptr, true, L.ctl->tile_ctr, s);
     CGA_PROF("rle", s);
-    k_rle<K, K, false><<<(unsigned)rle_tiles(n), kRleBlock, 0, s>>>(
-        fin, n, nullptr, 0, ~0ull, keys, counts, nullptr, cap, n_out, L.rle_status,
-        &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err);
+    rle_launch<K, K, false>(fin, n, nullptr, 0, ~0ull, keys, counts, nullptr, cap, n_out, L.rle_status,
+        &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err, s);
 }
 
 // Largest workspace any compiled tuning needs.
@@ -220,12 +219,11 @@ static void arrays_enqueue(const cga_grid *g, const K *keys, int64_t n, const in
     const int d = (int)g->depth;
     const uint64_t m = (1ull << d) - 1;
     K *xy = (K *)L.xy;
-    const unsigned tiles = (unsigned)rle_tiles(n);
     CGA_PROF("arrays", s);
-    k_rle<K, K, true><<<tiles, kRleBlock, 0, s>>>(keys, n, d_n, d, ~0ull, xy, nullptr, yp, n, nxy,
-                                                   L.st_xy, &L.ctl->tile_ctr[0], &L.ctl->err);
-    k_rle<K, uint32_t, true><<<tiles, kRleBlock, 0, s>>>(xy, n, nxy, d, m, xi, nullptr, xp, n, nx,
-                                                         L.st_x, &L.ctl->tile_ctr[1], &L.ctl->err);
+    rle_launch<K, K, true>(keys, n, d_n, d, ~0ull, xy, nullptr, yp, n, nxy,
+                                                   L.st_xy, &L.ctl->tile_ctr[0], &L.ctl->err, s);
+    rle_launch<K, uint32_t, true>(xy, n, nxy, d, m, xi, nullptr, xp, n, nx,
+                                                         L.st_x, &L.ctl->tile_ctr[1], &L.ctl->err, s);
     int64_t blocks = (n + 255) / 256;
     blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
     k_low_bits<K><<<(unsigned)blocks, 256, 0, s>>>(keys, n, d_n, m, zi);

@@ -61,7 +61,10 @@ __global__ __launch_bounds__(256) void k_encode(const float *__restrict__ xyz, i
 template <typename K, int RB>
 inline void encode_launch(const cga_grid *g, const float *xyz, int64_t n, K *keys, int passes,
                           uint32_t *hist, uint32_t *err, hipStream_t s) {
-    int64_t blocks = (n + 256 * 8 - 1) / (256 * 8);
+    // one step of points per thread while blocks are few (each flushes its
+    // histograms), two from 2^17 points on
+    const int64_t per = 256 * (n < ((int64_t)1 << 17) ? kEncodeUnroll : 2 * kEncodeUnroll);
+    int64_t blocks = (n + per - 1) / per;
     blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
     CGA_PROF("encode", s);
     k_encode<K, RB><<<(unsigned)blocks, 256, hist_lds_bytes(passes, RB), s>>>(

@@ -497,9 +497,8 @@ static void project_enqueue(const cga_grid *g, const K *keys, int64_t n, const i
     if (g->key_mode == CGA_KEY_LINEAR && drop == 2) {
         // (x<<2d | y<<d | z) >> d = x<<d | y: already ascending, just collapse
         CGA_PROF("rle", s);
-        k_rle<K, K2, false><<<(unsigned)rle_tiles(n), kRleBlock, 0, s>>>(
-            keys, n, d_n, (int)d, ~0ull, out, counts, nullptr, cap, n_out, L.rle_status,
-            &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err);
+        rle_launch<K, K2, false>(keys, n, d_n, (int)d, ~0ull, out, counts, nullptr, cap, n_out, L.rle_status,
+            &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err, s);
         return;
     }
     const SortWs &w = L.sort;
@@ -509,9 +508,8 @@ static void project_enqueue(const cga_grid *g, const K *keys, int64_t n, const i
     K2 *other = (w.passes & 1) ? a : b;
     sort_launch<K2>(w, a, fin, other, fin, n, d_n, true, L.ctl->tile_ctr, s);
     CGA_PROF("rle", s);
-    k_rle<K2, K2, false><<<(unsigned)rle_tiles(n), kRleBlock, 0, s>>>(
-        fin, n, d_n, 0, ~0ull, out, counts, nullptr, cap, n_out, L.rle_status,
-        &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err);
+    rle_launch<K2, K2, false>(fin, n, d_n, 0, ~0ull, out, counts, nullptr, cap, n_out, L.rle_status,
+        &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err, s);
 }
 
 template <typename K>

@@ -13,10 +13,18 @@
 namespace cga {
 
 constexpr int kRleBlock = 256;
-constexpr int kRleItems = 24;
-constexpr int kRleTile = kRleBlock * kRleItems;
-
-inline int64_t rle_tiles(int64_t n) { return n <= 0 ? 1 : (n + kRleTile - 1) / kRleTile; }
+// Keys per thread and tile, by the host size: a tile's life is a chain of
+// steps over its threads' keys, so few keys go to short tiles that fill more
+// CUs, and many to long ones with fewer look-backs (32-bit keys, 4 / 12 / 24
+// per thread: 20k 10.7 / 15.2 / 20.1 us, 400k 17.7 / 17.1 / 21.5, 800k 24.9 /
+// 19.1 / 22.2, 1.6M 36.9 / 25.4 / 24.8, 12M 156 / 78 / 60).
+inline int rle_items(int64_t n) {
+    return n <= (int64_t)1 << 18 ? 4 : (n <= (int64_t)5 << 18 ? 12 : 24);
+}
+inline int64_t rle_tiles(int64_t n) {
+    const int64_t tile = (int64_t)kRleBlock * rle_items(n);
+    return n <= 0 ? 1 : (n + tile - 1) / tile;
+}
 
 // status word: [flag:2][heads:31][latest head index + 1:31]
 constexpr uint64_t kRleAgg = 1ull << 62;
@@ -30,7 +38,7 @@ __device__ __forceinline__ int32_t rle_last(uint64_t s) { return (int32_t)(s & 0
 // v_i = in[i] >> shift.  Per run u (in order): vals[u] = v & out_mask, and
 // counts[u] = run length (COUNTS) or ends[u + 1] = one past the run's last
 // index with ends[0] = 0 (ENDS).  Either output pointer may be null.
-template <typename K, typename OV, bool ENDS>
+template <typename K, typename OV, bool ENDS, int kRleItems>
 __global__ __launch_bounds__(kRleBlock) void k_rle(const K *__restrict__ in, int64_t n_host,
                                                    const int64_t *d_n, int shift,
                                                    uint64_t out_mask, OV *__restrict__ vals,
@@ -38,6 +46,7 @@ __global__ __launch_bounds__(kRleBlock) void k_rle(const K *__restrict__ in, int
                                                    int64_t *__restrict__ ends, int64_t cap,
                                                    int64_t *n_out, uint64_t *status,
                                                    uint32_t *tile_ctr, uint32_t *err) {
+    constexpr int kRleTile = kRleBlock * kRleItems;
     __shared__ uint32_t s_tile;
     // logical slot j lives at j + j/16, so the blocked per-thread reads below
     // (16 consecutive slots per thread) do not all fall in one LDS bank
@@ -196,6 +205,23 @@ __global__ __launch_bounds__(kRleBlock) void k_rle(const K *__restrict__ in, int
         }
     }
 #undef SV
+}
+
+// Launches k_rle with the tile of n's size (status: rle_tiles(n) words).
+template <typename K, typename OV, bool ENDS>
+inline void rle_launch(const K *in, int64_t n, const int64_t *d_n, int shift, uint64_t out_mask,
+                       OV *vals, uint32_t *counts, int64_t *ends, int64_t cap, int64_t *n_out,
+                       uint64_t *status, uint32_t *tile_ctr, uint32_t *err, hipStream_t s) {
+    const unsigned tiles = (unsigned)rle_tiles(n);
+    auto launch = [&](auto kernel) {
+        kernel<<<tiles, kRleBlock, 0, s>>>(in, n, d_n, shift, out_mask, vals, counts, ends, cap,
+                                           n_out, status, tile_ctr, err);
+    };
+    switch (rle_items(n)) {
+        case 4: launch(k_rle<K, OV, ENDS, 4>); break;
+        case 12: launch(k_rle<K, OV, ENDS, 12>); break;
+        default: launch(k_rle<K, OV, ENDS, 24>); break;
+    }
 }
 
 }  // namespace cga

@@ -149,6 +149,24 @@ def test_build_capacity(gpu, w_c1):
     assert len(k) == len(wc)
 
 
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 3072, 3073, 1 << 18, (1 << 18) + 1, 5 << 18,
+                               (5 << 18) + 1])
+def test_build_run_tiles(gpu, n):
+    """Sizes at the edges of the run-length tiles and of the sizes that choose
+    them: keys and counts of a build, ends of the five arrays."""
+    rng = np.random.default_rng(n)
+    vox = np.stack([rng.integers(0, 64, n), rng.integers(0, 2048, n), rng.integers(0, 600, n)], 1)
+    for mode in (M, L):
+        g = Grid((0.0, 0.0, 0.0), 1.0, 11, mode)
+        k, c = gpu.cga_build(dev(vox.astype(np.float32)), g)
+        want, counts = np.unique(oracle.encode(vox, 11, mode), return_counts=True)
+        assert np.array_equal(u64(k), want) and np.array_equal(u32(c), counts)
+    arr = gpu.cga_to_arrays(k, g)
+    xy, ends = np.unique(want >> np.uint64(11), return_counts=True)
+    assert np.array_equal(arr["y_pointer"].cpu().numpy(), np.concatenate([[0], np.cumsum(ends)]))
+    assert np.array_equal(u32(arr["y_index"]), xy & np.uint64(2047))
+
+
 # ------------------------------------------------------------ paper arrays
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s"])
 def test_to_arrays(gpu, wl, request):
