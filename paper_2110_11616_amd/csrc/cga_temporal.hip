@@ -18,8 +18,7 @@
 // 3. matching: every predicted voxel moved back by its cluster's vector is
 //    matched to the reference voxel of least SAD over the four channels among
 //    those within `window` voxels on each axis (ties: smaller L1 offset, then
-//    smaller key), found by key searches -- one lower bound and a short scan
-//    per (x, y) column for LINEAR keys, one search per voxel for MORTON;
+//    smaller key), found by key searches;
 // 4. residual: predicted minus matched channels (int16), or the voxel's own
 //    channels with match -1 and SAD UINT32_MAX when it left the grid or found
 //    no reference voxel.
@@ -126,16 +125,60 @@ __global__ void k_km_seed(KmState *st) {
     }
 }
 
+// Sum of a value over the wave (six adds along DPP rows), on every lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+    x = dpp_add<0x111, 0xF>(x);  // row_shr:1, 2, 4, 8
+    x = dpp_add<0x112, 0xF>(x);
+    x = dpp_add<0x114, 0xF>(x);
+    x = dpp_add<0x118, 0xF>(x);
+    x = dpp_add<0x142, 0xA>(x);  // row_bcast:15, 31
+    x = dpp_add<0x143, 0xC>(x);
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // One pass over both frames: stop if the previous pass changed nothing,
 // else move to the previous pass's cluster means and assign every voxel.
-template <typename K>
+//
+// Bound: latency.  A pass over 2 x 0.5M voxels is a chain of loads (the state
+// and last pass's sums, then the keys), the sums of its waves and the adds of
+// its blocks, about 7 us beside the 2.5 us between launches.  So everything
+// the start may need is loaded before the first branch, a wave loads its
+// ROWS rows of keys at once, and it keeps per-lane sums of its rows' common
+// cluster (neighbouring keys are neighbouring voxels) that it adds up over
+// its lanes once; only voxels of other clusters take a sum of their own.
+// 100 passes and the match, 2 x 0.5M voxels on LINEAR keys: 1.41 -> 1.06 ms.
+// Frames of up to kKmSmall voxels take one row per wave: four waves of one
+// row then end sooner than one of four (50k points at depth 8, 50 passes and
+// the match: 359 against 462 us).
+constexpr int64_t kKmSmall = (int64_t)1 << 18;
+
+template <typename K, int kKmRows>
 __global__ __launch_bounds__(256) void k_km_assign(Frames<K> F, uint32_t depth, bool linear, int pass,
                                                    KmState *st) {
     const int f = blockIdx.y;
     KmState &S = st[f];
-    if (S.halt) return;  // block-uniform
     const int cur = pass % 3, prev = (pass + 2) % 3, next = (pass + 1) % 3;
-    if (pass > 0 && !S.changed[prev]) {  // the run ended with the previous pass
+    // pass 0 starts from the corners in cent[0]; pass t > 0 from the means
+    // of pass t - 1's clusters, an empty cluster keeping pass t - 1's centre
+    // (24 lanes divide, the block reads the results from LDS)
+    const int ck = (int)threadIdx.x / 3, ca = (int)threadIdx.x % 3;
+    const uint32_t halt = S.halt, moved = S.changed[prev];
+    unsigned long long n = 0, sa = 0;
+    double v0 = 0.0;
+    if (threadIdx.x < kCl * 3) {
+        v0 = S.cent[pass > 0 ? (pass + 1) & 1 : 0][ck][ca];
+#pragma unroll
+        for (int r = 0; r < kRep; ++r) {
+            n += S.cnt[prev][r][ck];
+            sa += S.sum[prev][r][ck][ca];
+        }
+    }
+    if (halt) return;  // block-uniform: only ever set by a launch before
+    if (pass > 0 && !moved) {  // the run ended with the previous pass
         if (blockIdx.x == 0 && threadIdx.x == 0) S.halt = 1;
         return;
     }
@@ -143,25 +186,13 @@ __global__ __launch_bounds__(256) void k_km_assign(Frames<K> F, uint32_t depth, 
     __shared__ uint32_t s_changed;
     for (int t = threadIdx.x; t < kCl * 4; t += blockDim.x) s_sum[t] = 0;
     if (threadIdx.x == 0) s_changed = 0;
-    // pass 0 starts from the corners in cent[0]; pass t > 0 from the means
-    // of pass t - 1's clusters, an empty cluster keeping pass t - 1's centre
-    // (24 lanes divide, the block reads the results from LDS)
     __shared__ double s_c[kCl * 3];
     if (threadIdx.x < kCl * 3) {
-        const int k = threadIdx.x / 3, a = threadIdx.x % 3;
-        const int before = pass > 0 ? (pass + 1) & 1 : 0;
-        unsigned long long n = 0, sa = 0;
-        if (pass > 0)
-#pragma unroll
-            for (int r = 0; r < kRep; ++r) {
-                n += S.cnt[prev][r][k];
-                sa += S.sum[prev][r][k][a];
-            }
-        const double v = n > 0 ? __ddiv_rn((double)sa, (double)n) : S.cent[before][k][a];
+        const double v = pass > 0 && n > 0 ? __ddiv_rn((double)sa, (double)n) : v0;
         s_c[threadIdx.x] = v;
         // block 0 keeps this pass's centres (for the next pass's empty
         // clusters and for the result)
-        if (blockIdx.x == 0 && pass > 0) S.cent[pass & 1][k][a] = v;
+        if (blockIdx.x == 0 && pass > 0) S.cent[pass & 1][ck][ca] = v;
     }
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) S.iters = pass + 1;
@@ -180,20 +211,27 @@ __global__ __launch_bounds__(256) void k_km_assign(Frames<K> F, uint32_t depth, 
         for (int a = 0; a < 3; ++a) c[k][a] = s_c[k * 3 + a];
     bool changed = false;
     const int lane = threadIdx.x & 63;
-    // whole waves step together, so that the sums can be gathered per wave:
-    // neighbouring keys are neighbouring voxels, so a wave rarely spans more
-    // than one or two clusters, and each cluster costs one reduction
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t base = wave * 64; base < F.n[f]; base += waves * 64) {
-        const int64_t i = base + lane;
-        const bool active = i < F.n[f];
-        Vox v{0, 0, 0};
-        int best = 0;
-        if (active) {
-            v = dec3((uint64_t)F.keys[f][i], depth, linear);
+    for (int64_t base = wave * (64 * kKmRows); base < F.n[f]; base += waves * (64 * kKmRows)) {
+        K key[kKmRows];
+        int old[kKmRows];
+#pragma unroll
+        for (int r = 0; r < kKmRows; ++r) {
+            const int64_t i = base + r * 64 + lane;
+            key[r] = i < F.n[f] ? F.keys[f][i] : K(0);
+            old[r] = pass > 0 && i < F.n[f] ? F.assign[f][i] : -1;
+        }
+        int common = 0;  // the cluster of the wave's first voxel
+        uint32_t ax = 0, ay = 0, az = 0, an = 0;
+#pragma unroll
+        for (int r = 0; r < kKmRows; ++r) {
+            const int64_t i = base + r * 64 + lane;
+            const bool active = i < F.n[f];
+            const Vox v = dec3((uint64_t)key[r], depth, linear);
             const double px = (double)v.x, py = (double)v.y, pz = (double)v.z;
             double bd = 0.0;
+            int best = 0;
 #pragma unroll
             for (int k = 0; k < kCl; ++k) {
                 const double dx = __dsub_rn(px, c[k][0]), dy = __dsub_rn(py, c[k][1]),
@@ -204,30 +242,35 @@ __global__ __launch_bounds__(256) void k_km_assign(Frames<K> F, uint32_t depth, 
                     best = k;
                 }
             }
-            if (pass == 0 || F.assign[f][i] != best) changed = true;
-            F.assign[f][i] = (uint8_t)best;
-        }
-        uint64_t rem = __ballot(active);
-        while (rem) {
-            const int leader = __ffsll((unsigned long long)rem) - 1;
-            const int k = __shfl(best, leader, 64);
-            const bool mine = active && best == k;
-            const uint64_t m = __ballot(mine);
-            // at most 64 coordinates below 2^21 each: 32-bit sums are exact
-            uint32_t sx = mine ? v.x : 0u, sy = mine ? v.y : 0u, sz = mine ? v.z : 0u;
-            for (int o = 32; o > 0; o >>= 1) {
-                sx += __shfl_xor(sx, o, 64);
-                sy += __shfl_xor(sy, o, 64);
-                sz += __shfl_xor(sz, o, 64);
+            if (active && old[r] != best) {
+                changed = true;
+                F.assign[f][i] = (uint8_t)best;
             }
-            if (lane == leader) {
-                atomicAdd(&s_sum[k * 4 + 0], (unsigned long long)sx);
-                atomicAdd(&s_sum[k * 4 + 1], (unsigned long long)sy);
-                atomicAdd(&s_sum[k * 4 + 2], (unsigned long long)sz);
-                atomicAdd(&s_sum[k * 4 + 3], (unsigned long long)__popcll(m));
+            if (r == 0) common = __builtin_amdgcn_readfirstlane(best);
+            // at most 64 * kKmRows coordinates below 2^21: 32-bit sums are exact
+            const bool with = active && best == common;
+            ax += with ? v.x : 0u;
+            ay += with ? v.y : 0u;
+            az += with ? v.z : 0u;
+            an += (uint32_t)__popcll(__ballot(with));
+            uint64_t rem = __ballot(active && best != common);
+            while (rem) {
+                const int leader = __ffsll((unsigned long long)rem) - 1;
+                const int k = __builtin_amdgcn_readlane(best, leader);
+                const bool mine = active && best == k;
+                const uint64_t m = __ballot(mine);
+                const uint32_t sx = wave_sum(mine ? v.x : 0u), sy = wave_sum(mine ? v.y : 0u),
+                               sz = wave_sum(mine ? v.z : 0u);
+                if (lane < 4)
+                    atomicAdd(&s_sum[k * 4 + lane], (unsigned long long)(lane == 0 ? sx : lane == 1 ? sy : lane == 2 ? sz : (uint32_t)__popcll(m)));
+                rem &= ~m;
             }
-            rem &= ~m;
         }
+        ax = wave_sum(ax);
+        ay = wave_sum(ay);
+        az = wave_sum(az);
+        if (lane < 4)
+            atomicAdd(&s_sum[common * 4 + lane], (unsigned long long)(lane == 0 ? ax : lane == 1 ? ay : lane == 2 ? az : an));
     }
     if (__ballot(changed) && (threadIdx.x & 63) == 0) s_changed = 1;
     __syncthreads();
@@ -268,6 +311,36 @@ __device__ __forceinline__ uint32_t chan_sad(uint32_t a, uint32_t b) {
     return s;
 }
 
+// First index in [lo, n) whose key is >= v, for one not far past lo: steps
+// that double, then a search of the last one.
+template <typename K>
+__device__ __forceinline__ int64_t lower_bound_from(const K *keys, int64_t lo, int64_t n, uint64_t v) {
+    int64_t step = 1;
+    while (lo + step <= n && (uint64_t)keys[lo + step - 1] < v) {
+        lo += step;
+        step <<= 1;
+    }
+    int64_t len = lo + step <= n ? step - 1 : n - lo;
+    while (len > 0) {
+        const int64_t half = len >> 1;
+        if ((uint64_t)keys[lo + half] < v) {
+            lo += half + 1;
+            len -= half + 1;
+        } else {
+            len = half;
+        }
+    }
+    return lo;
+}
+
+// Matching, a thread per predicted voxel.  Bound: dependent key probes, so
+// few searches start from the whole array: on LINEAR keys one per x of the
+// window, the columns of further y then from where the one before ended; on
+// MORTON keys one per aligned cell of at least the window's width (eight at
+// most), whose keys are then taken in turn.  With a search of the whole
+// array per (x, y) column, 0.5M voxels took 179 us on LINEAR keys (window 2),
+// 127 now; with one per voxel of the window, whole calls on MORTON keys 3.4
+// ms (depth 11, window 3, 20 passes), 0.96 now.
 template <typename K>
 __global__ __launch_bounds__(256) void k_match(const K *__restrict__ ref_keys,
                                                const uint32_t *__restrict__ ref_vals, int64_t n_ref,
@@ -305,28 +378,40 @@ __global__ __launch_bounds__(256) void k_match(const K *__restrict__ ref_keys,
         if (inside && n_ref > 0) {
             const int64_t zlo = r[2] - window > 0 ? r[2] - window : 0;
             const int64_t zhi = r[2] + window < top - 1 ? r[2] + window : top - 1;
-            for (int64_t x = r[0] - window; x <= r[0] + window; ++x) {
-                if (x < 0 || x >= top) continue;
-                for (int64_t y = r[1] - window; y <= r[1] + window; ++y) {
-                    if (y < 0 || y >= top) continue;
-                    const uint32_t lxy = (uint32_t)((x > r[0] ? x - r[0] : r[0] - x) + (y > r[1] ? y - r[1] : r[1] - y));
-                    if (linear) {
+            const int64_t xlo = r[0] - window > 0 ? r[0] - window : 0;
+            const int64_t xhi = r[0] + window < top - 1 ? r[0] + window : top - 1;
+            const int64_t ylo = r[1] - window > 0 ? r[1] - window : 0;
+            const int64_t yhi = r[1] + window < top - 1 ? r[1] + window : top - 1;
+            auto off = [](int64_t a, int64_t b) { return (uint32_t)(a > b ? a - b : b - a); };
+            if (linear) {
+                for (int64_t x = xlo; x <= xhi; ++x) {
+                    int64_t j = 0;
+                    for (int64_t y = ylo; y <= yhi; ++y) {
+                        const uint32_t lxy = off(x, r[0]) + off(y, r[1]);
                         // the column's z range is one run of LINEAR keys
                         const uint64_t k0 = enc3((uint32_t)x, (uint32_t)y, (uint32_t)zlo, depth, true);
                         const uint64_t k1 = enc3((uint32_t)x, (uint32_t)y, (uint32_t)zhi, depth, true);
-                        for (int64_t j = lower_bound_k(ref_keys, n_ref, k0); j < n_ref && (uint64_t)ref_keys[j] <= k1; ++j) {
-                            const int64_t z = (int64_t)((uint64_t)ref_keys[j] & (uint64_t)(top - 1));
-                            consider(j, lxy + (uint32_t)(z > r[2] ? z - r[2] : r[2] - z));
-                        }
-                    } else {
-                        for (int64_t z = zlo; z <= zhi; ++z) {
-                            const uint64_t key = enc3((uint32_t)x, (uint32_t)y, (uint32_t)z, depth, false);
-                            const int64_t j = lower_bound_k(ref_keys, n_ref, key);
-                            if (j < n_ref && (uint64_t)ref_keys[j] == key)
-                                consider(j, lxy + (uint32_t)(z > r[2] ? z - r[2] : r[2] - z));
-                        }
+                        j = y == ylo ? lower_bound_k(ref_keys, n_ref, k0) : lower_bound_from(ref_keys, j, n_ref, k0);
+                        for (; j < n_ref && (uint64_t)ref_keys[j] <= k1; ++j)
+                            consider(j, lxy + off((int64_t)((uint64_t)ref_keys[j] & (uint64_t)(top - 1)), r[2]));
                     }
                 }
+            } else {
+                int lev = 0;
+                while (((int64_t)1 << lev) < 2 * window + 1 && lev < (int)depth) ++lev;
+                for (int64_t cx = xlo >> lev; cx <= xhi >> lev; ++cx)
+                    for (int64_t cy = ylo >> lev; cy <= yhi >> lev; ++cy)
+                        for (int64_t cz = zlo >> lev; cz <= zhi >> lev; ++cz) {
+                            const uint64_t cell = enc3((uint32_t)cx, (uint32_t)cy, (uint32_t)cz, depth, false);
+                            const uint64_t k0 = cell << (3 * lev), k1 = k0 + ((1ull << (3 * lev)) - 1);
+                            for (int64_t j = lower_bound_k(ref_keys, n_ref, k0); j < n_ref; ++j) {
+                                const uint64_t k = (uint64_t)ref_keys[j];
+                                if (k > k1) break;
+                                const Vox v = dec3(k, depth, false);
+                                if (v.x >= xlo && v.x <= xhi && v.y >= ylo && v.y <= yhi && v.z >= zlo && v.z <= zhi)
+                                    consider(j, off(v.x, r[0]) + off(v.y, r[1]) + off(v.z, r[2]));
+                            }
+                        }
             }
         }
         match[i] = best;
@@ -376,8 +461,11 @@ static void temporal_launch(const cga_grid *g, const K *rk, const uint32_t *rv, 
         CGA_PROF("temporal_kmeans", s);
         k_km_bbox<K><<<grid, 256, 0, s>>>(F, g->depth, linear, L.st);
         k_km_seed<<<2, 64, 0, s>>>(L.st);
-        for (int pass = 0; pass < max_iter; ++pass)
-            k_km_assign<K><<<grid, 256, 0, s>>>(F, g->depth, linear, pass, L.st);
+        const bool small = (nr > np ? nr : np) <= kKmSmall;
+        for (int pass = 0; pass < max_iter; ++pass) {
+            if (small) k_km_assign<K, 1><<<grid, 256, 0, s>>>(F, g->depth, linear, pass, L.st);
+            else k_km_assign<K, 4><<<grid, 256, 0, s>>>(F, g->depth, linear, pass, L.st);
+        }
         k_motion<<<1, 64, 0, s>>>(L.st, cent, mv, iters, L.mv);
     }
     if (np > 0) {

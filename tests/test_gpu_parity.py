@@ -941,3 +941,25 @@ def test_temporal_edges(gpu):
         gpu.cga_temporal_predict(keys_dev(lref, gl), dev(lr.view(np.int32)), keys_dev(lpred, gl),
                                  dev(lp.view(np.int32)), gl, window=16)
     assert err.value.status == gpu.EINVAL
+
+
+@pytest.mark.parametrize("mode", [M, L])
+@pytest.mark.parametrize("n,depth,window,max_iter", [
+    (63, 4, 1, 9), (64, 7, 2, 9), (257, 7, 3, 9), (1025, 8, 15, 4), (5000, 6, 4, 30), (9001, 21, 2, 4),
+    (1 << 18, 9, 1, 3), ((1 << 18) + 1, 9, 2, 3)])
+def test_temporal_sizes(gpu, mode, n, depth, window, max_iter):
+    """Frames at the edges of a pass's rows (one or four per wave), windows
+    narrower and wider than the cells that MORTON keys are searched by and
+    cut by the grid's faces."""
+    rng = np.random.default_rng(n + depth + window)
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, mode)
+    side = 1 << depth
+    p = rng.integers(0, side, (3 * n, 2))
+    vox = np.stack([p[:, 0], p[:, 1], (p[:, 0] + p[:, 1]) // 2 % side], 1)
+    ref = np.unique(oracle.encode(vox, depth, mode))
+    ref = np.sort(rng.permutation(ref)[:n])
+    pred = np.unique(oracle.encode(np.clip(oracle.decode(ref, depth, mode).astype(np.int64) + [1, -1, 0], 0,
+                                           side - 1), depth, mode))
+    rvals = rng.integers(0, 2 ** 32, len(ref), dtype=np.uint64).astype(np.uint32)
+    pvals = rng.integers(0, 2 ** 32, len(pred), dtype=np.uint64).astype(np.uint32)
+    _temporal_check(gpu, g, ref, rvals, pred, pvals, window, max_iter)
