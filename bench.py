@@ -15,7 +15,7 @@ Workloads:
 Prints one JSON line.  value = build+merge points per second: input points
 of both clouds over the time of the build of both clouds and their merge,
 measured over `steps` graph replays of exactly that part (the roofline
-object is its dominant kernel, the radix sort pass).  ms_per_step is the
+object is its dominant kernel).  ms_per_step is the
 whole step (every part above, overlapped, one graph replay per step); the
 k-NN queries per second and their two rooflines are reported under "knn".
 Unless --no-c5, it also measures the learned index against binary search on
@@ -356,6 +356,16 @@ def library_sort_default(key_bytes, key_bits, n):
     return rb, items
 
 
+def by_buckets(pipe):
+    """Whether the library builds this workload's clouds by buckets (restated
+    here for the report): more than 24 key bits, 2^13 to 2^24 points (2^23
+    with 32-bit keys) and no sort chosen by the caller."""
+    bits = 3 * pipe.g.depth
+    top = 1 << (24 if bits > 32 else 23)
+    return (pipe.tune_build is None and bits > 24
+            and all((1 << 13) <= n <= top for n in (pipe.na, pipe.nb)))
+
+
 def algorithmic_bytes(label, pipe, counts, build_merge_only=False, rb=(8, 8)):
     """Bytes the method itself must move for a kernel label over one step
     (reads + writes of its essential inputs and outputs); build_merge_only
@@ -368,13 +378,23 @@ def algorithmic_bytes(label, pipe, counts, build_merge_only=False, rb=(8, 8)):
     ua, ub, um = counts[:3]
     ups = counts[3:] if not build_merge_only else []
     nproj = len(ups)
+    buckets = by_buckets(pipe)
+    if label == "bucket_sort":
+        # every key read, every run's value and length written
+        return kb * (pipe.na + pipe.nb) + (kb + 4) * (ua + ub) if buckets else None
+    if label == "bucket_scatter":
+        # every key and its bin read, every key written
+        return (2 * kb + 2) * (pipe.na + pipe.nb) if buckets else None
+    if label == "bucket_emit":
+        return 2 * (kb + 4) * (ua + ub) if buckets else None
     if label == "onesweep":
         # every pass reads and writes each key once
-        return passes3 * 2 * kb * (pipe.na + pipe.nb) + nproj * passes2 * 2 * k2b * um
+        return ((0 if buckets else passes3 * 2 * kb * (pipe.na + pipe.nb))
+                + nproj * passes2 * 2 * k2b * um)
     if label == "encode":
-        return (12 + kb) * (pipe.na + pipe.nb)
+        return (12 + kb + (2 if buckets else 0)) * (pipe.na + pipe.nb)
     if label == "rle":
-        return (kb * (pipe.na + pipe.nb) + (kb + 4) * (ua + ub)
+        return ((0 if buckets else kb * (pipe.na + pipe.nb) + (kb + 4) * (ua + ub))
                 + sum(k2b * um + (k2b + 4) * up for up in ups))
     if label == "merge":
         return kb * (ua + ub + um)
@@ -955,10 +975,12 @@ def main():
         raise RuntimeError("learned and binary lookups disagree")
     progress(f"warm-up done; counts {counts}")
 
+    # the kernel that dominates a build
+    build_label = "bucket_sort" if by_buckets(pipe) else "onesweep"
     if args.only:
         # one part only, launched `steps` times (profiler runs); the live
         # event timing of its main kernel is printed for comparison
-        part = {"build_merge": (pipe.build_merge_concurrent, "onesweep"),
+        part = {"build_merge": (pipe.build_merge_concurrent, build_label),
                 "step": (pipe.step_concurrent, "knn"), "knn": (pipe._knn, "knn")}[args.only]
         if not args.no_kernel_timing:
             cga.cga_prof_reset()
@@ -973,7 +995,8 @@ def main():
         return
 
     # per-kernel breakdown (untimed serial steps)
-    labels = ["begin", "encode", "histogram", "hist_scan", "onesweep", "rle", "merge_partition",
+    labels = ["begin", "bucket_sample", "encode", "bucket_scatter", "bucket_sort", "bucket_emit",
+              "histogram", "hist_scan", "onesweep", "rle", "merge_partition",
               "merge", "rekey", "knn_order", "knn_tree", "knn", "index_root", "index_bounds",
               "index_fit", "index_err", "index_lookup", "binary_lookup"]
     kern_ms = {}
@@ -997,7 +1020,7 @@ def main():
     n_points = pipe.na + pipe.nb
     bm_roof = None
     if not args.no_kernel_timing:
-        cga.cga_prof_enable(["onesweep"])
+        cga.cga_prof_enable([build_label])
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     e0.record()
@@ -1009,10 +1032,10 @@ def main():
     pipe.check()
     ms_bm_eager = e0.elapsed_time(e1) / args.steps
     if not args.no_kernel_timing:
-        bm_roof = roofline_from_prof("onesweep", algorithmic_bytes("onesweep", pipe, counts, True,
-                                                                   rbs),
-                                     args.steps, load_traffic("onesweep", args.workload),
-                                     "build+merge launched per run (both clouds' sort passes)")
+        bm_roof = roofline_from_prof(build_label, algorithmic_bytes(build_label, pipe, counts, True,
+                                                                    rbs),
+                                     args.steps, load_traffic(build_label, args.workload),
+                                     "build+merge launched per run (both clouds' sorts)")
         cga.cga_prof_reset()
     ms_bm = graph_replay(pipe, pipe.build_merge_concurrent, args.steps, False)
     progress(f"build+merge: eager {ms_bm_eager:.3f} ms, graph {ms_bm:.3f} ms")

@@ -3,6 +3,7 @@
 // helpers of the library.
 #include <cmath>
 
+#include "cga_bucket.h"
 #include "cga_common.h"
 #include "cga_rle.h"
 #include "cga_encode.h"
@@ -167,6 +168,35 @@ static void build_enqueue(const cga_grid *g, const float *xyz, int64_t n, K *key
         &L.ctl->tile_ctr[kMaxPasses], &L.ctl->err, s);
 }
 
+// Whether a build goes by buckets (cga_bucket.h) rather than by a sort of all
+// keys, where neither the caller nor the tuning cache chose a sort.  Three
+// 8-bit passes are no dearer than the buckets (24-bit keys, 20k to 1M points:
+// 42 to 84 us against 44 to 81), from four on the buckets win (us of a sort
+// against buckets: 30-bit keys 20k 50 / 44, 1M 101 / 87, 7M 283 / 244; 36-bit
+// 1M 125 / 90, 5M 303 / 183; 48-bit 1M 145 / 93, 10M 538 / 366) until 32-bit
+// keys in random order are so many that the partition writes scattered lines
+// (10M 343 / 375), and below some thousand points the extra launches show
+// (4096 points 44 / 49).
+static bool bucket_build(const cga_grid *g, int64_t n) {
+    const int bits = 3 * (int)g->depth;
+    return bits > 24 && n >= (1 << 13) && n <= ((int64_t)1 << (bits > 32 ? 24 : 23));
+}
+
+struct BucketLayout {
+    Control *ctl;
+    BkWs bk;
+    size_t bytes;
+};
+
+static BucketLayout bucket_layout(void *ws, const cga_grid *g, int64_t n) {
+    BucketLayout L;
+    Carve c(ws);
+    L.ctl = c.take<Control>(1);
+    bk_carve(c, L.bk, n, wide_keys(g->depth) ? 8 : 4);
+    L.bytes = c.size();
+    return L;
+}
+
 // Largest workspace any compiled tuning needs.
 template <typename F>
 static size_t max_over_cfgs(F layout_bytes) {
@@ -269,7 +299,11 @@ int cga_ws_status(const void *d_ws, cga_stream stream) {
 
 size_t cga_build_workspace_bytes(const cga_grid *g, int64_t n) {
     if (!grid_valid(g) || n < 0) return 0;
-    return max_over_cfgs([&](const SortCfg &c) { return build_layout(nullptr, g, n, c).bytes; });
+    const size_t m =
+        max_over_cfgs([&](const SortCfg &c) { return build_layout(nullptr, g, n, c).bytes; });
+    if (!bucket_build(g, n)) return m;
+    const size_t b = bucket_layout(nullptr, g, n).bytes;
+    return b > m ? b : m;
 }
 
 int cga_build(const cga_grid *g, const float *d_xyz, int64_t n, void *d_keys, uint32_t *d_counts,
@@ -281,9 +315,25 @@ int cga_build(const cga_grid *g, const float *d_xyz, int64_t n, void *d_keys, ui
     const bool wide = wide_keys(g->depth);
     SortCfg cfg;
     CGA_TRY(pick_cfg(tune, wide, n, &cfg, 3 * (int)g->depth));
+    hipStream_t s = (hipStream_t)stream;
     BuildLayout L = build_layout(d_ws, g, n, cfg);
     if (ws_bytes < L.bytes) return CGA_EWORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
+    if (bucket_build(g, n) && !tune &&
+        !tuned_sort_cfg(wide ? 8 : 4, 3 * (int)g->depth, n, &cfg)) {
+        const BucketLayout B = bucket_layout(d_ws, g, n);
+        if (ws_bytes >= B.bytes) {
+            int64_t *out = d_n_out ? d_n_out : &B.ctl->count;
+            CGA_TRY(launch_begin(B.ctl, B.bk.zero, B.bk.zero_bytes, nullptr, 0, out, s));
+            if (wide)
+                bk_launch<uint64_t>(g, d_xyz, n, B.bk, (uint64_t *)d_keys, d_counts, cap, out,
+                                    &B.ctl->err, s);
+            else
+                bk_launch<uint32_t>(g, d_xyz, n, B.bk, (uint32_t *)d_keys, d_counts, cap, out,
+                                    &B.ctl->err, s);
+            CGA_HIP(hipGetLastError());
+            return n_out_host ? finish_counts(B.ctl, s, out, n_out_host) : CGA_OK;
+        }
+    }
     int64_t *cnt_out = d_n_out ? d_n_out : &L.ctl->count;
     CGA_TRY(launch_begin(L.ctl, L.sort.hist, sort_zero_bytes(L.sort), L.rle_status,
                          (size_t)rle_tiles(n) * 8, cnt_out, s));

@@ -107,6 +107,58 @@ def _check_build(gpu, xyz, g, tune=None):
     return wk
 
 
+def _bucket_samples(n):
+    """Positions that the build by buckets samples (cga_bucket.h)."""
+    nb = max(min(-(-n // 1024), 512), -(-n // 4096))
+    i, m = np.arange(8 * nb, dtype=np.uint64), np.uint64(0xFFFFFFFF)
+    lo, hi = i * np.uint64(n) // np.uint64(8 * nb), (i + np.uint64(1)) * np.uint64(n) // np.uint64(8 * nb)
+    h = i * np.uint64(0x9E3779B9) & m
+    h = (h ^ (h >> np.uint64(16))) * np.uint64(0x85EBCA6B) & m
+    h = (h ^ (h >> np.uint64(13))) * np.uint64(0xC2B2AE35) & m
+    h ^= h >> np.uint64(16)
+    return (lo + h % (hi - lo)).astype(np.int64)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "same", "half_same", "few", "far", "unsampled"])
+@pytest.mark.parametrize("n,depth", [(8191, 10), (8192, 10), (99_001, 9), (262_145, 12),
+                                     (300_007, 21), (1_048_576, 11), (2_200_003, 14)])
+def test_build_buckets(gpu, n, depth, kind):
+    """The build by buckets against the oracle and against the radix sort:
+    equal keys, repeated splitters, spans above 32 bits, empty buckets, and
+    buckets that the sample missed."""
+    rng = np.random.default_rng(n)
+    g = Grid((0.0, 0.0, 0.0), 2.0 ** depth, depth, M if n % 2 else L)
+    p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
+    if kind == "same":
+        p[:] = 0.3
+    elif kind == "half_same":
+        p[rng.permutation(n)[: n // 2]] = 0.7
+    elif kind == "few":
+        p = p[rng.integers(0, 37, n)]
+    elif kind == "far":  # two clusters in opposite corners
+        p *= np.float32(2.0 ** -5)
+        p[::3] = 1 - p[::3]
+    elif kind == "unsampled":
+        at = _bucket_samples(n)
+        p = 0.5 + 0.5 * p
+        p[at] = rng.uniform(0, 0.25, (len(at), 3)).astype(np.float32)
+    say("build by buckets", n, depth, kind)
+    wk = _check_build(gpu, p, g)
+    k, _ = gpu.cga_build(dev(p), g, tune=(8, 16), counts=False)
+    assert np.array_equal(u64(k), wk)
+    if kind == "uniform":  # what does not fit the capacity is refused, what fits is written
+        cap = len(wk) // 2
+        out = torch.zeros(cap + 64, dtype=gpu.key_dtype(g), device="cuda")
+        with pytest.raises(gpu.CgaError) as e:
+            gpu.cga_build(dev(p), g, cap=cap, keys_out=out, counts=False)
+        assert e.value.status == gpu.ECAPACITY
+        assert np.array_equal(u64(out[:cap]), wk[:cap]) and not out[cap:].any()
+        p[n // 2] = np.inf
+        with pytest.raises(gpu.CgaError) as e:
+            gpu.cga_build(dev(p), g)
+        assert e.value.status == gpu.ENONFINITE
+
+
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s", "w_c3s"])
 @pytest.mark.parametrize("mode", [M, L])
 def test_build(gpu, wl, mode, request):
