@@ -24,6 +24,7 @@
 #include <mutex>
 #include <tuple>
 
+#include "cga_batch_bucket.h"
 #include "cga_common.h"
 #include "cga_merge.h"
 #include "cga_rle.h"
@@ -297,6 +298,7 @@ struct BatchLayout {
     int64_t merge_tiles_bound;
     int frame_bits;
     bool seg;  // each frame sorted on its own by its 3 * depth key bits
+    BbWs bb;   // builds by buckets only
     size_t bytes;
 };
 
@@ -319,16 +321,32 @@ static int batch_sort_bits(const cga_grid *g, int F) {
     return 3 * (int)g->depth + (batch_segmented(F) ? 0 : frame_bits_of(F));
 }
 
-static BatchLayout batch_layout(void *ws, const cga_grid *g, int F, int64_t n, const SortCfg &cfg) {
+// Whether the frames are built by buckets (cga_batch_bucket.h) where no sort was
+// chosen: from four radix passes on, as for a single build, and frames of 2^17
+// points on average.  Smaller frames leave few buckets each, whose differences
+// take more than 32 bits (us of the radix passes against buckets, 36-bit keys:
+// 64 frames of 8.5k 145 / 179, 8 of 66k 143 / 169, 2 of 275k 144 / 133, 12 of
+// 788k 505 / 419, 256 of 10k to 2M 4077 / 3114), and few points in all show the
+// launches (3 frames of 14k 103 / 120).
+static bool batch_buckets(const cga_grid *g, int F, int64_t n) {
+    return 3 * (int)g->depth > 24 && batch_segmented(F) && n / F >= (1 << 17) && n >= (1 << 19);
+}
+
+static BatchLayout batch_layout(void *ws, const cga_grid *g, int F, int64_t n, const SortCfg &cfg,
+                                bool buckets = false) {
     BatchLayout L;
     Carve c(ws);
     L.frame_bits = frame_bits_of(F);
     L.seg = batch_segmented(F);
     L.ctl = c.take<Control>(1);
-    sort_carve(c, L.sort, n, batch_sort_bits(g, F), cfg, L.seg ? F : 0);
-    L.rle_status = c.take<uint64_t>((size_t)rle_tiles(n));
-    L.buf_a = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
-    L.buf_b = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
+    if (buckets) {
+        bb_carve(c, L.bb, F, n, wide_keys(g->depth) ? 8 : 4);
+    } else {
+        sort_carve(c, L.sort, n, batch_sort_bits(g, F), cfg, L.seg ? F : 0);
+        L.rle_status = c.take<uint64_t>((size_t)rle_tiles(n));
+        L.buf_a = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
+        L.buf_b = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
+    }
     L.tile_off = c.take<int64_t>((size_t)F + 1);
     L.total_tiles = c.take<int64_t>(1);
     L.merge_tiles_bound = (2 * n + kMergeTile - 1) / kMergeTile + F + 1;
@@ -394,6 +412,7 @@ struct BatchArgs {
     void *ws;
     size_t ws_bytes;
     SortCfg cfg;
+    bool buckets = false;
 };
 
 static int batch_validate(const cga_grid *g, const float *xyz, const int64_t *off, int F,
@@ -412,17 +431,27 @@ template <typename K>
 static int batch_enqueue(const BatchArgs &a, hipStream_t s) {
     BatchLayout L = batch_layout(a.ws, &a.g, a.F, a.n, a.cfg);
     if (a.ws_bytes < L.bytes) return CGA_EWORKSPACE;
+    bool buckets = false;
+    if (a.buckets) {
+        const BatchLayout B = batch_layout(a.ws, &a.g, a.F, a.n, a.cfg, true);
+        buckets = a.ws_bytes >= B.bytes;
+        if (buckets) L = B;
+    }
     const int shift = 3 * (int)a.g.depth;
-    CGA_TRY(launch_begin(L.ctl, L.sort.hist, sort_zero_bytes(L.sort), L.merge_status,
+    CGA_TRY(launch_begin(L.ctl, buckets ? L.bb.gbin : L.sort.hist,
+                         buckets ? L.bb.zero_bytes : sort_zero_bytes(L.sort), L.merge_status,
                          (size_t)L.merge_tiles_bound * 8, nullptr, s));
-    {
+    if (!buckets) {
         // the rle status and the tail of the pair arrays start at zero too
         int64_t nz = (int64_t)(rle_tiles(a.n));
         k_fill_i64<<<64, 256, 0, s>>>((int64_t *)L.rle_status, nz, 0);
     }
     const int64_t n = a.n;
     int64_t *d_u = &L.ctl->count;
-    if (n > 0) {
+    if (buckets) {
+        bb_launch<K>(&a.g, a.xyz, a.off, a.F, n, L.bb, (K *)a.keys, a.counts, a.key_off, d_u,
+                     &L.ctl->err, s);
+    } else if (n > 0) {
         batch_encode_dispatch(L.sort.radix_bits, &a.g, a.xyz, a.off, a.F, n, L.buf_a, L.sort.passes,
                               L.seg, L.sort.hist, &L.ctl->err, s);
         uint64_t *fin = (L.sort.passes & 1) ? L.buf_b : L.buf_a;
@@ -539,6 +568,10 @@ size_t cga_batch_workspace_bytes(const cga_grid *g, int nframes, int64_t n) {
             size_t b = batch_layout(nullptr, g, nframes, n, c).bytes;
             m = b > m ? b : m;
         }
+    if (batch_buckets(g, nframes, n)) {
+        const size_t b = batch_layout(nullptr, g, nframes, n, SortCfg(), true).bytes;
+        m = b > m ? b : m;
+    }
     return m;
 }
 
@@ -556,6 +589,8 @@ int cga_batch_build_merge(const cga_grid *g, const float *d_xyz, const int64_t *
     BatchArgs a{*g, d_xyz, d_off, nframes, n, d_keys, d_counts, d_key_off, d_merged, d_merged_off,
                 d_merged_cnt, d_ws, ws_bytes, SortCfg()};
     CGA_TRY(resolve_cfg(tune, 8, batch_sort_bits(g, nframes), n, &a.cfg));
+    a.buckets = !tune && batch_buckets(g, nframes, n) &&
+                !tuned_sort_cfg(8, batch_sort_bits(g, nframes), n, &a.cfg);
     return batch_run(a, (hipStream_t)stream);
 }
 
@@ -571,6 +606,8 @@ int cga_batch_graph_create(const cga_grid *g, const float *d_xyz, const int64_t 
     BatchArgs a{*g, d_xyz, d_off, nframes, n, d_keys, d_counts, d_key_off, d_merged, d_merged_off,
                 d_merged_cnt, d_ws, ws_bytes, SortCfg()};
     CGA_TRY(resolve_cfg(tune, 8, batch_sort_bits(g, nframes), n, &a.cfg));
+    a.buckets = !tune && batch_buckets(g, nframes, n) &&
+                !tuned_sort_cfg(8, batch_sort_bits(g, nframes), n, &a.cfg);
     if (ws_bytes < batch_layout(nullptr, g, nframes, n, a.cfg).bytes) return CGA_EWORKSPACE;
     persistent_groups();  // query the device before capture
     hipStream_t cs;

@@ -237,24 +237,15 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_group_rank(const uint32_t *__re
 // ---------------------------------------------------------------- encode
 constexpr int kBkUnroll = 4;
 
-// Block b owns the points [b * chunk, (b + 1) * chunk).
+// Points [c0, c1) to keys and bins, the bins' counts to s_bin; s_split holds the
+// splitters padded with the largest value to p2, a power of two.  Returns
+// whether a coordinate is not finite.
 template <typename K>
-__global__ __launch_bounds__(kBkBlock) void k_bk_encode(const float *__restrict__ xyz, int64_t n,
-                                                        int64_t chunk, BkGrid g,
-                                                        const K *__restrict__ split, int nb, int p2,
-                                                        K *__restrict__ keys,
-                                                        uint16_t *__restrict__ ids, uint32_t *gbin,
-                                                        uint32_t *err) {
-    extern __shared__ uint64_t s_dyn[];
-    K *s_split = (K *)s_dyn;                   // p2, padded with the largest value
-    uint32_t *s_bin = (uint32_t *)(s_split + p2);  // 2 nb
-    const int m = nb - 1;
-    for (int i = threadIdx.x; i < p2; i += kBkBlock) s_split[i] = i < m ? split[i] : ~K(0);
-    for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) s_bin[i] = 0;
-    __syncthreads();
+__device__ __forceinline__ bool bk_encode_range(const float *__restrict__ xyz, int64_t c0, int64_t c1,
+                                                const BkGrid &g, const K *s_split, int p2,
+                                                K *__restrict__ keys, uint16_t *__restrict__ ids,
+                                                uint32_t *s_bin) {
     const float o[3] = {g.o0, g.o1, g.o2};
-    const int64_t c0 = (int64_t)blockIdx.x * chunk;
-    const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
     bool bad = false;
     for (int64_t i0 = c0 + threadIdx.x; i0 - threadIdx.x < c1; i0 += kBkUnroll * kBkBlock) {
         float p[kBkUnroll][3];
@@ -297,7 +288,27 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_encode(const float *__restrict_
             }
         }
     }
-    if (bad) set_err(err, ERR_NONFINITE);
+    return bad;
+}
+
+// Block b owns the points [b * chunk, (b + 1) * chunk).
+template <typename K>
+__global__ __launch_bounds__(kBkBlock) void k_bk_encode(const float *__restrict__ xyz, int64_t n,
+                                                        int64_t chunk, BkGrid g,
+                                                        const K *__restrict__ split, int nb, int p2,
+                                                        K *__restrict__ keys,
+                                                        uint16_t *__restrict__ ids, uint32_t *gbin,
+                                                        uint32_t *err) {
+    extern __shared__ uint64_t s_dyn[];
+    K *s_split = (K *)s_dyn;                       // p2
+    uint32_t *s_bin = (uint32_t *)(s_split + p2);  // 2 nb
+    for (int i = threadIdx.x; i < p2; i += kBkBlock) s_split[i] = i < nb - 1 ? split[i] : ~K(0);
+    for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) s_bin[i] = 0;
+    __syncthreads();
+    const int64_t c0 = (int64_t)blockIdx.x * chunk;
+    const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
+    if (bk_encode_range<K>(xyz, c0, c1, g, s_split, p2, keys, ids, s_bin))
+        set_err(err, ERR_NONFINITE);
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) {
         const uint32_t c = s_bin[i];
@@ -305,27 +316,27 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_encode(const float *__restrict_
     }
 }
 
-// Sums of the groups' bins, and the buckets' first slots, over all and per group.
-static __global__ __launch_bounds__(kBkBlock) void k_bk_scan(const uint32_t *__restrict__ gbin, int nb,
-                                                      uint32_t *__restrict__ bin,
-                                                      uint32_t *__restrict__ start,
-                                                      uint32_t *__restrict__ cursor) {
-    __shared__ uint32_t s_w[kBkWaves];
-    uint32_t carry = 0;
-    for (int i0 = 0; i0 < nb; i0 += kBkBlock) {
+// Sums of the groups' bins of buckets [b0, b1), and the buckets' first slots from
+// `first` on, over all groups and per group; the groups' tables have nb buckets.
+__device__ __forceinline__ void bk_scan_range(const uint32_t *__restrict__ gbin, int nb, int b0,
+                                              int b1, uint32_t first, uint32_t *__restrict__ bin,
+                                              uint32_t *__restrict__ start,
+                                              uint32_t *__restrict__ cursor, uint32_t *s_w) {
+    uint32_t carry = first;
+    for (int i0 = b0; i0 < b1; i0 += kBkBlock) {
         const int i = i0 + (int)threadIdx.x;
         uint32_t v[kBkXcds], sum = 0, eq = 0;
 #pragma unroll
         for (int g = 0; g < kBkXcds; ++g) {
             uint2 c = make_uint2(0, 0);
-            if (i < nb) c = ((const uint2 *)gbin)[(size_t)g * nb + i];
+            if (i < b1) c = ((const uint2 *)gbin)[(size_t)g * nb + i];
             v[g] = c.x;
             sum += c.x;
             eq += c.y;
         }
         uint32_t tot;
         uint32_t ex = carry + block_excl_sum<kBkBlock>(sum, s_w, &tot);
-        if (i < nb) {
+        if (i < b1) {
             bin[2 * i] = sum;
             bin[2 * i + 1] = eq;
             start[i] = ex;
@@ -339,18 +350,23 @@ static __global__ __launch_bounds__(kBkBlock) void k_bk_scan(const uint32_t *__r
     }
 }
 
-// The keys of block b's points to their buckets, tile by tile: a tile's keys are
-// counted per bucket in LDS, each bucket's share is taken from the group's
-// cursor at once, and the keys go to it in any order.
+static __global__ __launch_bounds__(kBkBlock) void k_bk_scan(const uint32_t *__restrict__ gbin, int nb,
+                                                      uint32_t *__restrict__ bin,
+                                                      uint32_t *__restrict__ start,
+                                                      uint32_t *__restrict__ cursor) {
+    __shared__ uint32_t s_w[kBkWaves];
+    bk_scan_range(gbin, nb, 0, nb, 0, bin, start, cursor, s_w);
+}
+
+// The keys of the points [c0, c1) to their buckets (nb of them, cursors of the
+// block's group), tile by tile: a tile's keys are counted per bucket in LDS, each
+// bucket's share is taken from its cursor at once, and the keys go to it in any
+// order.
 template <typename K>
-__global__ __launch_bounds__(kBkBlock) void k_bk_scatter(const K *__restrict__ keys,
-                                                         const uint16_t *__restrict__ ids,
-                                                         int64_t n, int64_t chunk, int iu, int nb,
-                                                         uint32_t *cursor, K *__restrict__ out) {
-    extern __shared__ uint32_t s_cnt[];
-    cursor += (size_t)(blockIdx.x % kBkXcds) * nb;
-    const int64_t c0 = (int64_t)blockIdx.x * chunk;
-    const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
+__device__ __forceinline__ void bk_scatter_range(const K *__restrict__ keys,
+                                                 const uint16_t *__restrict__ ids, int64_t c0,
+                                                 int64_t c1, int iu, int nb, uint32_t *cursor,
+                                                 K *__restrict__ out, uint32_t *s_cnt) {
     for (int64_t t0 = c0; t0 < c1; t0 += (int64_t)iu * kBkBlock) {
         for (int i = threadIdx.x; i < nb; i += kBkBlock) s_cnt[i] = 0;
         __syncthreads();
@@ -391,6 +407,18 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_scatter(const K *__restrict__ k
             if (!(at[u] & 1u)) out[s_cnt[(at[u] & 0xFFFFu) >> 1] + (at[u] >> 16)] = k[u];
         __syncthreads();
     }
+}
+
+template <typename K>
+__global__ __launch_bounds__(kBkBlock) void k_bk_scatter(const K *__restrict__ keys,
+                                                         const uint16_t *__restrict__ ids,
+                                                         int64_t n, int64_t chunk, int iu, int nb,
+                                                         uint32_t *cursor, K *__restrict__ out) {
+    extern __shared__ uint32_t s_cnt[];
+    const int64_t c0 = (int64_t)blockIdx.x * chunk;
+    const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
+    bk_scatter_range<K>(keys, ids, c0, c1, iu, nb, cursor + (size_t)(blockIdx.x % kBkXcds) * nb, out,
+                        s_cnt);
 }
 
 // ------------------------------------------------------------------ sort
@@ -771,7 +799,7 @@ __global__ __launch_bounds__(kBkBlock, 8) void k_bk_sort(K *vals, K *tmp, int nb
     // the splitters bound the bucket; one that is open on a side looks for its
     // least and largest key
     uint64_t lo0 = 0, span = 0;
-    if (b > 0 && b < (uint32_t)nb - 1 && split[b] != ~K(0)) {
+    if (b > 0 && b < (uint32_t)nb - 1 && split[b - 1] != ~K(0) && split[b] != ~K(0)) {
         lo0 = (uint64_t)split[b - 1];
         span = (uint64_t)split[b] - lo0;
     } else if (cnt) {
@@ -816,7 +844,8 @@ __global__ __launch_bounds__(kBkBlock, 8) void k_bk_sort(K *vals, K *tmp, int nb
 }
 
 // The runs of every bucket, and the splitter's behind them, to their final
-// places; a block sums the numbers of the buckets before its own.
+// places, from the buckets' first places (bases) or, if null, the sum of the
+// numbers before them.
 template <typename K>
 __global__ __launch_bounds__(256) void k_bk_emit(const K *__restrict__ vals,
                                                  const K *__restrict__ tmp, int nb,
@@ -824,13 +853,19 @@ __global__ __launch_bounds__(256) void k_bk_emit(const K *__restrict__ vals,
                                                  const uint32_t *__restrict__ bin,
                                                  const K *__restrict__ split,
                                                  const uint32_t *__restrict__ uniq,
+                                                 const uint32_t *__restrict__ bases,
                                                  K *__restrict__ keys, uint32_t *__restrict__ counts,
                                                  int64_t cap, int64_t *n_out, uint32_t *err) {
     __shared__ uint32_t s_w[4];
     const int b = blockIdx.x;
-    uint32_t before = 0, base;
-    for (int i = threadIdx.x; i < b; i += 256) before += uniq[i] + (bin[2 * i + 1] ? 1u : 0u);
-    block_excl_sum<256>(before, s_w, &base);
+    uint32_t base;
+    if (bases) {
+        base = bases[b];
+    } else {
+        uint32_t before = 0;
+        for (int i = threadIdx.x; i < b; i += 256) before += uniq[i] + (bin[2 * i + 1] ? 1u : 0u);
+        block_excl_sum<256>(before, s_w, &base);
+    }
     const uint32_t u = uniq[b], first = start[b], n_eq = bin[2 * b + 1];
     const uint32_t *len = (const uint32_t *)(tmp + first);
     for (uint32_t r = threadIdx.x; r < u && (int64_t)base + r < cap; r += 256) {
@@ -897,7 +932,7 @@ inline void bk_launch(const cga_grid *g, const float *xyz, int64_t n, const BkWs
                                                          counts ? 1 : 0);
     }
     CGA_PROF("bucket_emit", s);
-    k_bk_emit<K><<<(unsigned)w.nb, 256, 0, s>>>(b, a, w.nb, w.start, w.bin, split, w.uniq, keys,
+    k_bk_emit<K><<<(unsigned)w.nb, 256, 0, s>>>(b, a, w.nb, w.start, w.bin, split, w.uniq, nullptr, keys,
                                                 counts, cap, n_out, err);
 }
 

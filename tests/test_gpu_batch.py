@@ -114,6 +114,44 @@ def test_batch_many_frames_composite_sort(gpu):
         _check(gpu, dict(xyz=xyz, off=off, grid=g), out)
 
 
+@pytest.mark.parametrize("kind", ["uniform", "same", "few", "far"])
+@pytest.mark.parametrize("depth,mode", [(9, gen.KEY_MORTON), (10, gen.KEY_LINEAR),
+                                        (12, gen.KEY_MORTON), (20, gen.KEY_LINEAR)])
+def test_batch_buckets(gpu, depth, mode, kind):
+    """Frames built by buckets (2^17 points or more on average): empty
+    frames at either end and inside, one point, one bucket and one point more,
+    frames over several blocks; against the oracle, and replayed as a graph."""
+    g = gen.Grid((0.0, 0.0, 0.0), 2.0 ** depth, depth, mode)
+    rng = np.random.default_rng(depth)
+    sizes = [0, 1, 8191, 8192, 0, 30_000, 1_200_001, 4096, 70_003, 0]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(off[-1])
+    p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
+    if kind == "same":
+        p[:] = 0.3
+    elif kind == "few":
+        p = p[rng.integers(0, 37, n)]
+    elif kind == "far":
+        p *= np.float32(2.0 ** -5)
+        p[::3] = 1 - p[::3]
+    say("batch by buckets", depth, kind)
+    xyz, doff = dev(p), dev(off)
+    out = gpu.cga_batch_build_merge(xyz, doff, g)
+    _check(gpu, dict(xyz=p, off=off, grid=g), out)
+    u = int(out.key_off[-1].item())
+    graph = gpu.BatchGraph(xyz, doff, g)
+    for _ in range(2):
+        graph.out.keys.fill_(0)
+        graph.launch()
+        torch.cuda.synchronize()
+        assert graph.status() == 0
+        assert torch.equal(graph.out.keys[:u], out.keys[:u])
+        assert torch.equal(graph.out.counts[:u], out.counts[:u])
+        assert torch.equal(graph.out.key_off, out.key_off)
+        assert torch.equal(graph.out.merged_cnt, out.merged_cnt)
+    graph.close()
+
+
 def test_graph_replays_match_eager(gpu, frames):
     xyz, off, g = dev(frames["xyz"]), dev(frames["off"]), frames["grid"]
     ref = gpu.cga_batch_build_merge(xyz, off, g)
