@@ -95,8 +95,9 @@ int cga_ws_status(const void *d_ws, cga_stream stream);
 
 /* ------------------------------------------------------------------ build
  * CGA construction (Section V): quantize n float32 points (AoS x,y,z) by
- * the grid rule, encode each voxel as a key, radix-sort the keys and collapse
- * equal keys.  Output: the U unique keys ascending in d_keys (capacity cap)
+ * the grid rule, encode each voxel as a key, sort the keys and collapse equal
+ * keys (by sampled buckets where that is faster and tune is NULL with no choice
+ * recorded by the autotuner; otherwise by a radix sort).  Output: the U unique keys ascending in d_keys (capacity cap)
  * and, if d_counts is non-NULL, the number of input points in each voxel
  * (uint32).  U goes to d_n_out / n_out_host.  n may be 0.
  * Errors: CGA_ENONFINITE (device), CGA_ECAPACITY if U > cap (device). */

@@ -1,6 +1,7 @@
 // Batched CGA construction of F frames and the union of every consecutive
 // frame pair, sized entirely on the device so the whole sequence can be
-// captured once in a hipGraph and replayed:
+// captured once in a hipGraph and replayed (large frames take steps 1 to 4 by
+// buckets, cga_batch_bucket.h):
 //   1. quantize + encode every point as the composite key (frame << 3d | key)
 //      with the digit histograms of the sort on the side;
 //   2. an LSD radix sort segmented by frame: each frame's keys sorted on
