@@ -175,12 +175,14 @@ __device__ __forceinline__ int64_t lower_bound_u(const K *keys, int64_t n, uint6
     return lo;
 }
 
-// key_off[f] = first unique composite key of frame >= f, f = 0..F.
+// key_off[f] = first unique composite key of frame >= f, f = 0..F.  The end
+// of the last frame is the number of keys, not a search: where the frame bits
+// end at bit 64 and F is a power of two, F << shift is 0.
 __global__ void k_batch_offsets(const uint64_t *__restrict__ comp, const int64_t *d_u, int F,
                                 int shift, int64_t *__restrict__ key_off) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f > F) return;
-    key_off[f] = lower_bound_u(comp, *d_u, (uint64_t)f << shift);
+    key_off[f] = f == F ? *d_u : lower_bound_u(comp, *d_u, (uint64_t)f << shift);
 }
 
 template <typename K>

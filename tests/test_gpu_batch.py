@@ -114,6 +114,31 @@ def test_batch_many_frames_composite_sort(gpu):
         _check(gpu, dict(xyz=xyz, off=off, grid=g), out)
 
 
+@pytest.mark.parametrize("depth,nf", [(21, 2), (20, 16), (19, 128), (16, 65536)])
+def test_batch_frame_bits_end_at_64(gpu, depth, nf):
+    """As many frames as the composite key has room for: the last frame's end
+    (key_off[F]) is the number of keys, so every pair's length is right."""
+    rng = np.random.default_rng(depth)
+    sizes = rng.integers(0, 3, nf) if nf > 1000 else rng.integers(1, 3000, nf)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    p = rng.uniform(0, 1, (int(off[-1]), 3)).astype(np.float32)
+    p[-1] = 1.0  # the largest key in the last frame: all 64 bits set
+    g = gen.Grid((0.0, 0.0, 0.0), 2.0 ** depth, depth, gen.KEY_MORTON)
+    say("batch of", nf, "frames at depth", depth)
+    for tune in (None, (8, 16)):
+        out = gpu.cga_batch_build_merge(dev(p), dev(off), g, tune=tune)
+        ko = out.key_off.cpu().numpy()
+        mo, mc = out.merged_off.cpu().numpy(), out.merged_cnt.cpu().numpy()
+        keys, merged = u64(out.keys), u64(out.merged)
+        assert (np.diff(ko) >= 0).all() and ko[-1] <= len(p)
+        for f in range(nf - 1) if nf < 1000 else (0, 1, nf // 2, nf - 3, nf - 2):
+            want = [oracle.build(p[off[i]:off[i + 1]], g)[0] for i in (f, f + 1)]
+            for i in (0, 1):
+                assert np.array_equal(keys[ko[f + i]:ko[f + i + 1]], want[i]), f
+            wm, _ = oracle.merge(want[0], want[1], g.depth, g.key_mode)
+            assert mc[f] == len(wm) and np.array_equal(merged[mo[f]:mo[f] + mc[f]], wm), f
+
+
 @pytest.mark.parametrize("kind", ["uniform", "same", "few", "far"])
 @pytest.mark.parametrize("depth,mode", [(9, gen.KEY_MORTON), (10, gen.KEY_LINEAR),
                                         (12, gen.KEY_MORTON), (20, gen.KEY_LINEAR)])
