@@ -346,7 +346,7 @@ static BatchLayout batch_layout(void *ws, const cga_grid *g, int F, int64_t n, c
         bb_carve(c, L.bb, F, n, wide_keys(g->depth) ? 8 : 4);
     } else {
         sort_carve(c, L.sort, n, batch_sort_bits(g, F), cfg, L.seg ? F : 0);
-        L.rle_status = c.take<uint64_t>((size_t)rle_tiles(n));
+        L.rle_status = c.take<uint64_t>((size_t)rle_status_words(n));
         L.buf_a = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
         L.buf_b = c.take<uint64_t>((size_t)(n > 0 ? n : 1));
     }

@@ -136,7 +136,7 @@ static BuildLayout build_layout(void *ws, const cga_grid *g, int64_t n, const So
     const size_t kb = wide_keys(g->depth) ? 8 : 4;
     L.ctl = c.take<Control>(1);
     sort_carve(c, L.sort, n, 3 * (int)g->depth, cfg);
-    L.rle_status = c.take<uint64_t>((size_t)rle_tiles(n));
+    L.rle_status = c.take<uint64_t>((size_t)rle_status_words(n));
     L.buf_a = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
     L.buf_b = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
     L.bytes = c.size();
@@ -233,8 +233,8 @@ static ArraysLayout arrays_layout(void *ws, const cga_grid *g, int64_t n) {
     ArraysLayout L;
     Carve c(ws);
     L.ctl = c.take<Control>(1);
-    L.st_xy = c.take<uint64_t>((size_t)rle_tiles(n));
-    L.st_x = c.take<uint64_t>((size_t)rle_tiles(n));
+    L.st_xy = c.take<uint64_t>((size_t)rle_status_words(n));
+    L.st_x = c.take<uint64_t>((size_t)rle_status_words(n));
     L.xy = c.take<char>((size_t)(n > 0 ? n : 1) * (wide_keys(g->depth) ? 8 : 4));
     L.bytes = c.size();
     return L;

@@ -473,7 +473,7 @@ static ProjLayout proj_layout(void *ws, const cga_grid *g, int64_t n, const Sort
     const size_t kb = wide_keys2(g->depth) ? 8 : 4;
     L.ctl = c.take<Control>(1);
     sort_carve(c, L.sort, n, 2 * (int)g->depth, cfg);
-    L.rle_status = c.take<uint64_t>((size_t)rle_tiles(n));
+    L.rle_status = c.take<uint64_t>((size_t)rle_status_words(n));
     L.buf_a = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
     L.buf_b = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
     if (proj_by_tiles(g)) {

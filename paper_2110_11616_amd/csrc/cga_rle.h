@@ -25,6 +25,15 @@ inline int64_t rle_tiles(int64_t n) {
     const int64_t tile = (int64_t)kRleBlock * rle_items(n);
     return n <= 0 ? 1 : (n + tile - 1) / tile;
 }
+// Status words to carve: the most tiles of any array of up to n keys (the tiles
+// grow at the sizes above, where their number falls), so that a workspace of n's
+// size holds every smaller call.
+inline int64_t rle_status_words(int64_t n) {
+    int64_t m = rle_tiles(n);
+    for (const int64_t edge : {(int64_t)1 << 18, (int64_t)5 << 18})
+        if (n > edge && rle_tiles(edge) > m) m = rle_tiles(edge);
+    return m;
+}
 
 // status word: [flag:2][heads:31][latest head index + 1:31]
 constexpr uint64_t kRleAgg = 1ull << 62;
@@ -207,7 +216,7 @@ __global__ __launch_bounds__(kRleBlock) void k_rle(const K *__restrict__ in, int
 #undef SV
 }
 
-// Launches k_rle with the tile of n's size (status: rle_tiles(n) words).
+// Launches k_rle with the tile of n's size (status: rle_tiles(n) zeroed words).
 template <typename K, typename OV, bool ENDS>
 inline void rle_launch(const K *in, int64_t n, const int64_t *d_n, int shift, uint64_t out_mask,
                        OV *vals, uint32_t *counts, int64_t *ends, int64_t cap, int64_t *n_out,

@@ -70,6 +70,35 @@ def test_key_widths_and_workspace_queries(lib):
     assert lib.cga_merge_workspace_bytes(ctypes.byref(grid(12)), 10, 10) >= 256
 
 
+@pytest.mark.parametrize("depth", [1, 6, 10, 12, 14, 16, 21])
+def test_workspace_bytes_never_fall(lib, depth):
+    """A workspace sized for n holds every smaller call: no size falls as n
+    grows (steps of the tile sizes, the bucket builds' ends and powers of two)."""
+    P, I64, SZ = ctypes.c_void_p, ctypes.c_int64, ctypes.c_size_t
+    ns = sorted({n + e for b in range(2, 28) for n in (1 << b, 3 << b, 5 << b) for e in (-1, 0, 1)})
+    two = lambda f, *first: lambda g, n: f(g, *first, n)
+    calls = {}
+    for name in ("build", "sort", "to_arrays", "project", "occupancy", "voxel_values"):
+        f = getattr(lib, f"cga_{name}_workspace_bytes")
+        f.restype, f.argtypes = SZ, [P, I64]
+        calls[name] = f
+    for name in ("merge", "knn"):
+        f = getattr(lib, f"cga_{name}_workspace_bytes")
+        f.restype, f.argtypes = SZ, [P, I64, I64]
+        calls[name] = two(f, 1000)
+        calls[name + " first"] = lambda g, n, f=f: f(g, n, 1000)
+    f = lib.cga_batch_workspace_bytes
+    f.restype, f.argtypes = SZ, [P, ctypes.c_int, I64]
+    for frames in (1, 2, 256, 4097):
+        calls[f"batch {frames}"] = two(f, frames)
+    for mode in (0, 1):
+        g = grid(depth, mode)
+        for name, f in calls.items():
+            sizes = [f(ctypes.byref(g), n) for n in ns]
+            fell = [n for n, a, b in zip(ns[1:], sizes, sizes[1:]) if b < a]
+            assert sizes[0] > 0 and not fell, (name, fell)
+
+
 def test_batch_sort_bits(lib):
     """The batched sort covers the 3 * depth key bits when it is segmented
     by frame (up to 4096 frames), the frame bits too beyond that."""
