@@ -459,6 +459,7 @@ struct ProjLayout {
     void *buf_a, *buf_b;
     TileTables tiles{};
     size_t tile_bytes = 0;  // of the tables to clear, contiguous from tiles.cells
+    size_t sort_bytes;      // what the sort alone needs
     size_t bytes;
 };
 
@@ -476,6 +477,7 @@ static ProjLayout proj_layout(void *ws, const cga_grid *g, int64_t n, const Sort
     L.rle_status = c.take<uint64_t>((size_t)rle_status_words(n));
     L.buf_a = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
     L.buf_b = c.take<char>((size_t)(n > 0 ? n : 1) * kb);
+    L.sort_bytes = c.size();
     if (proj_by_tiles(g)) {
         const uint32_t lev = tile_level(g->depth), tiles = proj_tiles(g->depth);
         L.tiles.cells = c.take<uint2>((size_t)tiles << (g->depth - lev));
@@ -597,16 +599,17 @@ int cga_project(const cga_grid *g, const void *d_keys, int64_t n, const int64_t 
         if (!sort_cfg_supported(cfg)) return CGA_EINVAL;
     }
     ProjLayout L = proj_layout(d_ws, g, n, cfg);
-    if (ws_bytes < L.bytes) return CGA_EWORKSPACE;
+    if (ws_bytes < L.sort_bytes) return CGA_EWORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     int64_t *cnt_out = d_n_out ? d_n_out : &L.ctl->count;
-    // A caller that names a sort setting gets the sort.  So does one that does
-    // not wait and has few voxels to a tile: the sort's launches then follow
+    // A caller that names a sort setting, or whose workspace holds the sort
+    // but not the tile tables, gets the sort.  So does one that does not wait
+    // and has few voxels to a tile: the sort's launches then follow
     // the tiles' (k_proj_redo), about 15 us whatever the size, and the tiles'
     // own share does not shrink with the voxels (up to 400k at depth 14 the
     // pair is 6 % slower than the sort alone; 3M 1.4x as fast).
     const bool wide = wide_keys(g->depth);
-    const bool tiles = !tune && n > 0 && proj_by_tiles(g) &&
+    const bool tiles = !tune && n > 0 && proj_by_tiles(g) && ws_bytes >= L.bytes &&
                        (n_out_host || n >= (int64_t)proj_tiles(g->depth) * 64);
     auto sort_way = [&](const int64_t *count) {
         if (wide)

@@ -457,6 +457,42 @@ def test_project_tiles(gpu, depth, axis):
             _project_both(gpu, _key_tensor(ks, depth), g, axis, want, counts)
 
 
+class _Exactly:
+    """Workspaces of one fixed size, whatever is asked for."""
+
+    def __init__(self, nbytes):
+        self.buf = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+
+    def get(self, name, nbytes):
+        return self.buf
+
+
+@pytest.mark.parametrize("depth", [6, 12, 14])
+def test_project_workspace_of_the_sort(gpu, depth):
+    """A workspace that holds the sort but not the tile tables (what a LINEAR
+    grid of the same sizes asks for) is accepted, waiting or not; one that does
+    not hold the sort either is refused."""
+    import ctypes
+    rng = np.random.default_rng(depth)
+    n = 20_000
+    g = Grid((0.0, 0.0, 0.0), 1.0, depth, M)
+    need = lambda grid: gpu.lib.cga_project_workspace_bytes(ctypes.byref(gpu.grid_struct(grid)), n)
+    sort_need = need(g.with_mode(L))
+    assert sort_need < need(g)
+    ks = np.sort(rng.choice(1 << min(3 * depth, 40), n, replace=False).astype(np.uint64))
+    uv = np.delete(oracle.decode(ks, depth, M), 2, 1)
+    want, counts = np.unique(oracle.encode2(uv[:, 0], uv[:, 1], depth, M), return_counts=True)
+    keys = keys_dev(ks, g)
+    out, cnt = gpu.cga_project(keys, g, 2, ws=_Exactly(sort_need))
+    assert np.array_equal(u64(out), want) and np.array_equal(u32(cnt), counts)
+    d = torch.zeros(1, dtype=torch.int64, device="cuda")
+    out, cnt, _ = gpu.cga_project(keys, g, 2, d_n_out=d, sync=False, ws=_Exactly(sort_need))
+    assert int(d) == len(want) and np.array_equal(u64(out[:len(want)]), want)
+    with pytest.raises(gpu.CgaError) as e:
+        gpu.cga_project(keys, g, 2, ws=_Exactly(n * 4))
+    assert e.value.status == gpu.EWORKSPACE
+
+
 @pytest.mark.parametrize("n", [1024, 1025, 65_535, 65_536, 200_000, 262_144, 262_145])
 def test_project_tile_totals(gpu, n):
     """One tile's voxels around the limits of its ways to count them (bitmap,
