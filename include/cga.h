@@ -139,7 +139,9 @@ int cga_to_arrays(const cga_grid *grid, const void *d_keys, int64_t n, const int
  * n_xy of Y_index (Y_pointer n_xy + 1), n of Z_index.  d_n_x / d_n_xy are
  * optional device counts (at most the host bounds), so that the arrays can
  * stay on the device.  Pointer entries outside those lengths raise
- * CGA_EMISMATCH (device) and are clamped, so every access stays in bounds.
+ * CGA_EMISMATCH (device) where a search reads them, and are clamped, so every
+ * access stays in bounds; cga_arrays_nn looks at all of them while n_x + n_xy
+ * is at most 2^21 per query.
  * CGA_EMISMATCH (host) for a MORTON grid.  Workspace:
  * cga_arrays_ops_workspace_bytes() bytes (the call's error block). */
 size_t cga_arrays_ops_workspace_bytes(void);

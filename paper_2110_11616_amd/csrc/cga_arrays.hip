@@ -125,17 +125,20 @@ __global__ __launch_bounds__(256) void k_arrays_lookup(Arrays A, const uint32_t 
 // LiDAR cloud (depth 12) took 1.3 to 2.1 ms so, 0.2 ms outwards.
 constexpr int kNnTeam = 8;
 constexpr int kNnBlock = 256;
+// Every pointer entry is looked at, those that no query's walk reaches too,
+// while there are at most this many to a query: a pass over 8 bytes an entry,
+// about 1.3M entries a us.  Beyond it only the entries that the walks read are
+// (one query on 17M entries: 37 us with the pass, 16 without; 1.6M: 16 and 14).
+constexpr int64_t kNnLookPerQuery = (int64_t)1 << 21;
 
 __global__ __launch_bounds__(kNnBlock) void k_arrays_nn(Arrays A, const float *__restrict__ q,
-                                                        int64_t nq, float o0, float o1, float o2,
-                                                        float scale, uint32_t depth,
+                                                        int64_t nq, bool look_all, float o0, float o1,
+                                                        float o2, float scale, uint32_t depth,
                                                         int64_t *__restrict__ idx,
                                                         uint64_t *__restrict__ d2) {
     __shared__ unsigned long long s_bd[kNnBlock / kNnTeam];
     A.resolve();
-    // every pointer entry is looked at once, those that no query's walk
-    // reaches too (a few bytes per query at most)
-    for (int64_t i = (int64_t)blockIdx.x * kNnBlock + threadIdx.x; i < A.nx + A.nxy;
+    for (int64_t i = (int64_t)blockIdx.x * kNnBlock + threadIdx.x; look_all && i < A.nx + A.nxy;
          i += (int64_t)gridDim.x * kNnBlock) {
         int64_t lo, hi;
         if (i < A.nx) A.y_run(i, lo, hi);
@@ -285,10 +288,12 @@ int cga_arrays_nn(const cga_grid *g, const uint32_t *d_x_index, int64_t n_x, con
         const Arrays A{d_x_index, d_x_ptr, d_y_index, d_y_ptr, d_z_index, n_x, n_xy, n,
                        d_n_x, d_n_xy, &ctl->err};
         // blocks for the queries, and enough to look at every pointer entry
-        // with at most eight per thread
-        const unsigned qb = arrays_grid(nq * kNnTeam), pb = arrays_grid((n_x + n_xy + 7) / 8);
-        k_arrays_nn<<<qb > pb ? qb : pb, kNnBlock, 0, s>>>(
-            A, d_q, nq, g->origin[0], g->origin[1], g->origin[2], g->scale, g->depth, d_idx, d_d2);
+        // (if they are looked at) with at most eight per thread
+        const bool look_all = (n_x + n_xy - 1) / kNnLookPerQuery < nq;
+        const unsigned qb = arrays_grid(nq * kNnTeam), pb = arrays_grid(look_all ? (n_x + n_xy + 7) / 8 : 1);
+        k_arrays_nn<<<qb > pb ? qb : pb, kNnBlock, 0, s>>>(A, d_q, nq, look_all, g->origin[0],
+                                                           g->origin[1], g->origin[2], g->scale,
+                                                           g->depth, d_idx, d_d2);
     }
     CGA_HIP(hipGetLastError());
     return CGA_OK;

@@ -358,6 +358,30 @@ def test_arrays_nn_outward(gpu, shape, depth):
     np.testing.assert_array_equal(idx.cpu().numpy(), widx[:, 0])
 
 
+def test_arrays_nn_few_queries_read_what_they_walk(gpu):
+    """A call looks at every pointer entry while there are at most 2^21 of
+    them per query; one query on a larger array reads those of its walk alone,
+    so a broken entry far from it neither costs nor raises anything."""
+    side = 1449  # side * side (x, y) runs and side x entries
+    assert 1 << 21 < side * side + side < 2 << 21
+    g = Grid((0.0, 0.0, 0.0), 1.0, 11, L)
+    x, y = np.divmod(np.arange(side * side, dtype=np.uint64), np.uint64(side))
+    keys = (x << np.uint64(22)) | (y << np.uint64(11)) | ((x + y) & np.uint64(7))
+    arr = gpu.cga_to_arrays(keys_dev(keys, g), g)
+    assert len(arr["y_index"]) == side * side
+    arr["y_pointer"][-5] = 1 << 40  # where the run of (side - 1, side - 4) begins
+    q = np.array([[10.0, 20.0, 3.0], [5.0, 6.0, 0.0]], np.float32)
+    want, wd2 = oracle.knn_kdtree(keys, q, g, 1)
+    idx, d2 = gpu.cga_arrays_nn(arr, dev(q[:1]), g)
+    assert int(idx[0]) == want[0, 0] and int(d2[0]) == wd2[0, 0]
+    with pytest.raises(gpu.CgaError) as e:
+        gpu.cga_arrays_nn(arr, dev(q), g)
+    assert e.value.status == gpu.EMISMATCH
+    with pytest.raises(gpu.CgaError) as e:  # a query in that run walks it
+        gpu.cga_arrays_nn(arr, dev(np.array([[side - 1, side - 4, 0]], np.float32)), g)
+    assert e.value.status == gpu.EMISMATCH
+
+
 # ------------------------------------------------------------------- merge
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s", "w_c3s"])
 @pytest.mark.parametrize("mode", [M, L])
