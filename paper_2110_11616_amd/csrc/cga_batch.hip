@@ -325,25 +325,33 @@ static int batch_sort_bits(const cga_grid *g, int F) {
 }
 
 // Whether the frames are built by buckets (cga_batch_bucket.h) where no sort was
-// chosen: from four radix passes on, as for a single build, and frames of 2^17
-// points on average.  Smaller frames leave few buckets each, whose differences
-// take more than 32 bits (us of the radix passes against buckets, 36-bit keys:
-// 64 frames of 8.5k 145 / 179, 8 of 66k 143 / 169, 2 of 275k 144 / 133, 12 of
-// 788k 505 / 419, 256 of 10k to 2M 4077 / 3114), and few points in all show the
-// launches (3 frames of 14k 103 / 120).
+// chosen: from four radix passes on, as for a single build, and frames of 2^17 to
+// 2^22 points on average, above 42 key bits 3 * 2^20 (us of the radix passes
+// against buckets, LiDAR sweeps of 36-bit keys: 64 frames of 8.5k 145 / 179, 8 of
+// 66k 143 / 169, 12 of 788k 505 / 419, 256 of 10k to 2M 4081 / 3088; surfaces in
+// random order, which leave scattered lines: 2 of 4M 36-bit 505 / 458, 42-bit 554 /
+// 532, 48-bit 570 / 645; 2 of 3M 48-bit 488 / 483; 2 of 5M 39-bit 593 / 613; 2 of 8M
+// 36-bit 836 / 1024, where LiDAR is at 712 / 621).  One frame may be larger than
+// that: 8M points among 20 of 150k 689 / 703, 30M among 20 of 500k 2076 / 2125.
+// Few points in all show the launches (3 frames of 14k 103 / 120).
+constexpr int64_t kBbFrame = (int64_t)1 << 22, kBbFrameWide = (int64_t)3 << 20;
+
 static bool batch_buckets(const cga_grid *g, int F, int64_t n) {
-    return 3 * (int)g->depth > 24 && batch_segmented(F) && n / F >= (1 << 17) && n >= (1 << 19);
+    const int bits = 3 * (int)g->depth;
+    return bits > 24 && batch_segmented(F) && n / F >= (1 << 17) && n >= (1 << 19) &&
+           n <= F * (bits > 42 ? kBbFrameWide : kBbFrame);
 }
 
+// most: points per bucket of a build by buckets, 0 for the sort.
 static BatchLayout batch_layout(void *ws, const cga_grid *g, int F, int64_t n, const SortCfg &cfg,
-                                bool buckets = false) {
+                                int most = 0) {
     BatchLayout L;
     Carve c(ws);
     L.frame_bits = frame_bits_of(F);
     L.seg = batch_segmented(F);
     L.ctl = c.take<Control>(1);
-    if (buckets) {
-        bb_carve(c, L.bb, F, n, wide_keys(g->depth) ? 8 : 4);
+    if (most) {
+        bb_carve(c, L.bb, F, n, wide_keys(g->depth) ? 8 : 4, most);
     } else {
         sort_carve(c, L.sort, n, batch_sort_bits(g, F), cfg, L.seg ? F : 0);
         L.rle_status = c.take<uint64_t>((size_t)rle_status_words(n));
@@ -436,7 +444,8 @@ static int batch_enqueue(const BatchArgs &a, hipStream_t s) {
     if (a.ws_bytes < L.bytes) return CGA_EWORKSPACE;
     bool buckets = false;
     if (a.buckets) {
-        const BatchLayout B = batch_layout(a.ws, &a.g, a.F, a.n, a.cfg, true);
+        const BatchLayout B =
+            batch_layout(a.ws, &a.g, a.F, a.n, a.cfg, bb_most(a.F, a.n, 3 * (int)a.g.depth));
         buckets = a.ws_bytes >= B.bytes;
         if (buckets) L = B;
     }
@@ -571,8 +580,11 @@ size_t cga_batch_workspace_bytes(const cga_grid *g, int nframes, int64_t n) {
             size_t b = batch_layout(nullptr, g, nframes, n, c).bytes;
             m = b > m ? b : m;
         }
-    if (batch_buckets(g, nframes, n)) {
-        const size_t b = batch_layout(nullptr, g, nframes, n, SortCfg(), true).bytes;
+    // nor less than the largest n up to this one that may go by buckets asks
+    // for, with the most buckets: a workspace for n holds every smaller batch
+    const int64_t most = (int64_t)nframes * kBbFrame, nb = n < most ? n : most;
+    if (3 * (int)g->depth > 24 && batch_segmented(nframes)) {
+        const size_t b = batch_layout(nullptr, g, nframes, nb, SortCfg(), kBbLeast).bytes;
         m = b > m ? b : m;
     }
     return m;

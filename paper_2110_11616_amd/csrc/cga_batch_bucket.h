@@ -8,10 +8,30 @@
 
 namespace cga {
 
-constexpr int kBbMax = 2048;  // buckets of one frame: 4096 points each up to 8M points
+constexpr int kBbMax = 4096;       // buckets of one frame: 4096 points each up to 16M points
+constexpr int kBbSamples = 16384;  // samples of one frame that its block sorts
+
+// Points per bucket of F frames of n points in all: 4096, or, of few points whose
+// average bucket spans 30 key bits or more, what gives two buckets a CU.  A
+// bucket beyond 32 bits (Morton neighbours across a high bit) is sorted by 64-bit
+// passes, and above 7168 keys (3 % of them at 4096 on average) through global
+// memory: 100 us and more that few other buckets hide (us at 4096 / so, surfaces
+// in random order: 600k 42-bit keys 169 / 116, 4 frames of 300k, 36 bits 228 / 162,
+// 16 of 150k, 42 bits 305 / 230; LiDAR sweeps 104 / 110, 167 / 158, 262 / 214).
+// From kBbFew on others do, and more buckets cost the LiDAR sweeps 5 %.
+constexpr int kBbLeast = 1024, kBbWideMost = 2560;
+constexpr int64_t kBbFew = (int64_t)kBbWideMost * 2048;
+inline int bb_most(int F, int64_t n, int bits) {
+    int lg = 0;
+    while (((int64_t)8192 << lg) <= n / F) ++lg;
+    if (bits - lg < 30 || n > kBbFew) return 4096;
+    const int64_t fill = n / 512;
+    return (int)(fill < kBbLeast ? kBbLeast : (fill < kBbWideMost ? fill : kBbWideMost));
+}
 
 struct BbWs {
     int nb = 0;                  // bound on the buckets of all frames
+    int most = 0;                // points per bucket
     uint32_t *gbin = nullptr, *bin = nullptr;  // zeroed: per group and in all 2 nb
     size_t zero_bytes = 0;
     int32_t *fb = nullptr;       // F + 1: first bucket of each frame
@@ -21,8 +41,9 @@ struct BbWs {
     void *a = nullptr, *b = nullptr;
 };
 
-inline void bb_carve(Carve &c, BbWs &w, int F, int64_t n, size_t kb) {
-    w.nb = (int)(n / 4096 + F);
+inline void bb_carve(Carve &c, BbWs &w, int F, int64_t n, size_t kb, int most) {
+    w.most = most;
+    w.nb = (int)(n / most + F);
     w.gbin = c.take<uint32_t>((size_t)kBkXcds * 2 * w.nb);
     w.bin = c.take<uint32_t>((size_t)2 * w.nb);
     w.fb = c.take<int32_t>((size_t)F + 1);
@@ -37,15 +58,15 @@ inline void bb_carve(Carve &c, BbWs &w, int F, int64_t n, size_t kb) {
     w.b = c.take<char>((size_t)n * kb);
 }
 
-// First bucket of every frame: one per 4096 points, at least one, at most
+// First bucket of every frame: one per `most` points, at least one, at most
 // kBbMax.  One block.
 __global__ __launch_bounds__(kBkBlock) void k_bb_plan(const int64_t *__restrict__ off, int F,
-                                                      int32_t *__restrict__ fb) {
+                                                      int most, int32_t *__restrict__ fb) {
     __shared__ int32_t s_w[kBkWaves];
     int32_t carry = 0;
     for (int f0 = 0; f0 < F; f0 += kBkBlock) {
         const int f = f0 + (int)threadIdx.x;
-        int64_t b = f < F ? (off[f + 1] - off[f]) / 4096 : 0;
+        int64_t b = f < F ? (off[f + 1] - off[f]) / most : 0;
         b = b < 1 ? 1 : (b > kBbMax ? kBbMax : b);
         int32_t tot;
         const int32_t ex = block_excl_sum<kBkBlock>(f < F ? (int32_t)b : 0, s_w, &tot);
@@ -56,18 +77,22 @@ __global__ __launch_bounds__(kBkBlock) void k_bb_plan(const int64_t *__restrict_
 }
 
 // A block per frame: its samples sorted, its splitters at equal distances among
-// them.
+// them.  (Its LDS is a CU's; the blocks are short and few.)
 template <typename K>
 __global__ __launch_bounds__(kBkBlock) void k_bb_sample(const float *__restrict__ xyz,
                                                         const int64_t *__restrict__ off, BkGrid g,
                                                         const int32_t *__restrict__ fb,
                                                         K *__restrict__ split) {
-    __shared__ K s_k[kBkOneSort];
+    __shared__ K s_k[kBbSamples];
     const int f = blockIdx.x, b0 = fb[f], nb = fb[f + 1] - b0;
     const int64_t first = off[f], n = off[f + 1] - first;
     if (threadIdx.x == 0) split[b0 + nb - 1] = ~K(0);
     if (nb < 2) return;
-    const int S = nb * kBkOver < kBkOneSort ? nb * kBkOver : kBkOneSort;
+    // eight a bucket up to 4096 (50 us), then as many more as leave three a
+    // bucket: with one or two, frames of 8M to 60M points among smaller ones
+    // took 1.2 to 1.7 times as long as by the radix passes, so 1.0 to 1.2
+    int S = nb * kBkOver < kBkOneSort ? nb * kBkOver : kBkOneSort;
+    while (S < 3 * nb && S < kBbSamples) S *= 2;
     int p2 = 2;
     while (p2 < S) p2 <<= 1;
     for (int i = threadIdx.x; i < p2; i += kBkBlock) {
@@ -216,7 +241,7 @@ inline void bb_launch(const cga_grid *g, const float *xyz, const int64_t *off, i
     const int64_t chunk = (n + blocks - 1) / blocks;
     {
         CGA_PROF("bucket_sample", s);
-        k_bb_plan<<<1, kBkBlock, 0, s>>>(off, F, w.fb);
+        k_bb_plan<<<1, kBkBlock, 0, s>>>(off, F, w.most, w.fb);
         k_bb_sample<K><<<(unsigned)F, kBkBlock, 0, s>>>(xyz, off, bg, w.fb, split);
     }
     {

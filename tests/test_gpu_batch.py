@@ -177,6 +177,44 @@ def test_batch_buckets(gpu, depth, mode, kind):
     graph.close()
 
 
+@pytest.mark.parametrize("depth,sizes,buckets", [
+    (12, [3_000_000, 20_000], True),            # above 2^21: fewer than eight samples a bucket
+    (12, [150_000, 9_000_000, 150_000], True),  # one large frame among small ones: 2197 buckets
+    (10, [100_000, 17_500_000, 0, 60_000, 40_000], True),  # more than 4096 points to each of 4096
+    (14, [600_000], True),                      # few points, wide spans: 1171 points a bucket
+    (12, [1 << 22], True), (12, [(1 << 22) + 1], False),      # the rule's ends
+    (15, [3 << 20], True), (15, [(3 << 20) + 1], False),
+    (12, [1 << 17] * 3 + [(1 << 17) + 1], True), (12, [1 << 17] * 3 + [(1 << 17) - 1], False)])
+def test_batch_bucket_frames(gpu, depth, sizes, buckets):
+    """Which batches go by buckets, and every frame against its own build by the
+    radix sort."""
+    rng = torch.Generator(device="cuda").manual_seed(depth)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(off[-1])
+    p = torch.rand((n, 3), generator=rng, device="cuda")
+    p[::2, 2] = 0.25 + 0.5 * p[::2, 0] * p[::2, 1]  # half of them on a surface
+    g = gen.Grid((0.0, 0.0, 0.0), 2.0 ** depth, depth, gen.KEY_MORTON)
+    say("batch of", sizes[:3], "at depth", depth)
+    gpu.cga_prof_enable(["bucket_sort", "onesweep"])
+    gpu.cga_prof_reset()
+    try:
+        out = gpu.cga_batch_build_merge(p, dev(off), g)
+        torch.cuda.synchronize()
+        assert (gpu.cga_prof_read("bucket_sort")[1] > 0) == buckets
+        assert (gpu.cga_prof_read("onesweep")[1] > 0) == (not buckets)
+    finally:
+        gpu.cga_prof_disable()
+        gpu.cga_prof_reset()
+    ko, frames = out.key_off.cpu().tolist(), []
+    for f, m in enumerate(sizes):
+        k, c = gpu.cga_build(p[off[f]:off[f + 1]].contiguous(), g, tune=(8, 16))
+        assert torch.equal(out.keys[ko[f]:ko[f + 1]], k), f
+        assert torch.equal(out.counts[ko[f]:ko[f + 1]], c), f
+        frames.append(k.clone())
+    for f in range(len(sizes) - 1):
+        assert torch.equal(out.pair(f), gpu.cga_merge(frames[f], frames[f + 1], g)[0]), f
+
+
 def test_graph_replays_match_eager(gpu, frames):
     xyz, off, g = dev(frames["xyz"]), dev(frames["off"]), frames["grid"]
     ref = gpu.cga_batch_build_merge(xyz, off, g)
