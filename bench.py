@@ -358,10 +358,10 @@ def library_sort_default(key_bytes, key_bits, n):
 
 def by_buckets(pipe):
     """Whether the library builds this workload's clouds by buckets (restated
-    here for the report): more than 24 key bits, 2^13 to 2^24 points (2^23
+    here for the report): more than 24 key bits, 2^13 to 10 * 2^20 points (2^23
     with 32-bit keys) and no sort chosen by the caller."""
     bits = 3 * pipe.g.depth
-    top = 1 << (24 if bits > 32 else 23)
+    top = 10 << 20 if bits > 32 else 1 << 23
     return (pipe.tune_build is None and bits > 24
             and all((1 << 13) <= n <= top for n in (pipe.na, pipe.nb)))
 

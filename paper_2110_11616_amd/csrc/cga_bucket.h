@@ -11,17 +11,22 @@
 //   4. scatter: the keys to their buckets, in any order; keys that equal a
 //      splitter are one run and are only counted.
 //   5. sort: a block per bucket subtracts the bucket's lower bound, sorts the
-//      differences by 8-bit digits in LDS and finds the runs.  A
-//      bucket over kBkCap keys, or half of that where the difference takes
-//      more than 32 bits, is sorted through global memory by its block,
-//      slowly; the sample makes one improbable for any input (its positions
-//      do not depend on the data, and repeated keys become splitters).
+//      differences in LDS and finds the runs.  A bucket over kBkCap keys, or
+//      half of that where the difference takes more than 32 bits, is sorted
+//      through global memory by its block, slowly.  With eight samples a bucket
+//      (at hashed positions, repeated keys made splitters) one of 4096 keys on
+//      average is over kBkCap with probability 3e-7, over the half with 3 %:
+//      2M to 10M points of wide spans (a filled volume, or a surface of 14 bits
+//      an axis and more in random order) have some tens of those and still gain
+//      (filled volume of 63-bit keys, us of a sort against buckets: 2M 262 / 217,
+//      4M 406 / 305, 8M 583 / 507).
 //   6. emit: the buckets' runs to their places in the output.
 // Measured, 10M points of a surface in random order, 42-bit keys: sample 31 us,
 // encode 88, scan 7, scatter 94 (1.9 TB/s; 128 with a range per block instead of
 // the shared cursors), sort 157 (LDS and barriers; 392 with a look-back for the
 // place of its output), emit 54 (4.4 TB/s): 431 against 515 of six radix passes
-// and a compaction.  1M LiDAR points, 36 bits: 84 against 126.
+// and a compaction (kernel times; the calls take 474 and 514).  1M LiDAR points,
+// 36 bits: 84 against 126.
 #pragma once
 
 #include "cga_common.h"
@@ -45,7 +50,7 @@ constexpr int kBkGrid = 512;                 // encode and scatter blocks: two p
 constexpr int kBkXcds = 8;
 
 // Buckets for n points: 1024 points each while that is at most two per CU,
-// then 4096 (a bucket of eight samples exceeds kBkCap with probability 3e-7).
+// then 4096.
 inline int bk_buckets(int64_t n) {
     int64_t b = (n + 1023) / 1024;
     b = b < 512 ? b : 512;

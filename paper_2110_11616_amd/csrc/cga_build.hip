@@ -173,13 +173,17 @@ static void build_enqueue(const cga_grid *g, const float *xyz, int64_t n, K *key
 // 8-bit passes are no dearer than the buckets (24-bit keys, 20k to 1M points:
 // 42 to 84 us against 44 to 81), from four on the buckets win (us of a sort
 // against buckets: 30-bit keys 20k 50 / 44, 1M 101 / 87, 7M 283 / 244; 36-bit
-// 1M 125 / 90, 5M 303 / 183; 48-bit 1M 145 / 93, 10M 538 / 366) until 32-bit
-// keys in random order are so many that the partition writes scattered lines
-// (10M 343 / 375), and below some thousand points the extra launches show
-// (4096 points 44 / 49).
+// 1M 125 / 90, 5M 303 / 183; 48-bit 1M 145 / 93, 10M 538 / 366) until the points
+// in random order are so many that the partition writes scattered lines: 32-bit
+// keys 8M 294 / 270, 10M 343 / 375; wider ones 10M 538 / 540 at 48 bits and 514 /
+// 474 at 42, 12M 608 / 637 and 580 / 574, 16M 763 / 825 and 727 / 755 (LiDAR
+// sweeps, in order, would gain on: 16M 736 / 523 at 42 bits).  Below some thousand
+// points the extra launches show (4096 points 44 / 49).
+constexpr int64_t kBucketLeast = 1 << 13, kBucketMost32 = 1 << 23, kBucketMost = 10 << 20;
+
 static bool bucket_build(const cga_grid *g, int64_t n) {
     const int bits = 3 * (int)g->depth;
-    return bits > 24 && n >= (1 << 13) && n <= ((int64_t)1 << (bits > 32 ? 24 : 23));
+    return bits > 24 && n >= kBucketLeast && n <= (bits > 32 ? kBucketMost : kBucketMost32);
 }
 
 struct BucketLayout {

@@ -159,6 +159,40 @@ def test_build_buckets(gpu, n, depth, kind):
         assert e.value.status == gpu.ENONFINITE
 
 
+def _routes(gpu, labels, call):
+    """Launches of each kernel label during a call."""
+    gpu.cga_prof_enable(labels)
+    gpu.cga_prof_reset()
+    try:
+        call()
+        torch.cuda.synchronize()
+        return [gpu.cga_prof_read(name)[1] for name in labels]
+    finally:
+        gpu.cga_prof_disable()
+        gpu.cga_prof_reset()
+
+
+@pytest.mark.parametrize("n,depth,mode,buckets", [
+    ((1 << 13) - 1, 12, M, False), (1 << 13, 12, L, True), (100_000, 8, M, False),
+    (1 << 23, 10, M, True), ((1 << 23) + 1, 10, M, False),
+    (10 << 20, 12, L, True), (10 << 20, 16, M, True), ((10 << 20) + 1, 16, M, False),
+    (5_000_001, 21, M, True), (5_000_001, 21, L, True)])
+def test_build_bucket_ends(gpu, n, depth, mode, buckets):
+    """Which builds go by buckets, at the rule's ends and with millions of wide
+    spans (some buckets beyond what LDS holds), against the radix sort."""
+    rng = torch.Generator(device="cuda").manual_seed(n)
+    p = torch.rand((n, 3), generator=rng, device="cuda")
+    p[::2, 2] = 0.25 + 0.5 * p[::2, 0] * p[::2, 1]  # half of them on a surface
+    g = Grid((0.0, 0.0, 0.0), 2.0 ** depth, depth, mode)
+    say("build of", n, "at depth", depth)
+    got = []
+    by_buckets, by_sort = _routes(gpu, ["bucket_sort", "onesweep"],
+                                  lambda: got.extend(gpu.cga_build(p, g)))
+    assert (by_buckets > 0, by_sort > 0) == (buckets, not buckets)
+    want = gpu.cga_build(p, g, tune=(8, 16))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s", "w_c3s"])
 @pytest.mark.parametrize("mode", [M, L])
 def test_build(gpu, wl, mode, request):
