@@ -96,8 +96,8 @@ int cga_ws_status(const void *d_ws, cga_stream stream);
 /* ------------------------------------------------------------------ build
  * CGA construction (Section V): quantize n float32 points (AoS x,y,z) by
  * the grid rule, encode each voxel as a key, sort the keys and collapse equal
- * keys (by sampled buckets where that is faster and tune is NULL with no choice
- * recorded by the autotuner; otherwise by a radix sort).  Output: the U unique keys ascending in d_keys (capacity cap)
+ * keys (by sampled buckets where that is faster and tune is NULL; otherwise by a
+ * radix sort).  Output: the U unique keys ascending in d_keys (capacity cap)
  * and, if d_counts is non-NULL, the number of input points in each voxel
  * (uint32).  U goes to d_n_out / n_out_host.  n may be 0.
  * Errors: CGA_ENONFINITE (device), CGA_ECAPACITY if U > cap (device). */
@@ -432,18 +432,20 @@ int cga_mlp_loss_grad(const float *d_params, const float *d_x, const float *d_t,
  *       d_keys[d_key_off[f] .. d_key_off[f+1]);
  *   d_merged (capacity 2n): pair f's union starts at d_merged_off[f]
  *       (nframes - 1 int64) and holds d_merged_cnt[f] keys.
- * Implementation: composite keys (frame << 3*depth | key), a radix sort
- * segmented by frame (each frame's keys sorted within the frame's range by
- * the 3*depth key bits alone; above 4096 frames one sort of the composite
- * keys, frame bits included), one run-length pass, per-frame offsets by
- * binary search, then one persistent merge launch over a window queue
- * spanning all pairs.  Every size
+ * Implementation: frames of 2^17 to some million points on average by sampled
+ * buckets per frame where tune is NULL; otherwise composite keys (frame <<
+ * 3*depth | key), a radix sort segmented by frame (each frame's keys sorted
+ * within the frame's range by the 3*depth key bits alone; above 4096 frames one
+ * sort of the composite keys, frame bits included), one run-length pass and
+ * per-frame offsets by binary search.  Then one persistent merge launch over a
+ * window queue spanning all pairs.  Every size
  * after the input stays on the device, so the call can be captured in a
  * graph: cga_batch_graph_create records it once (on a private stream) into
  * an executable graph that cga_batch_graph_launch replays on any stream,
  * with the same buffers.  Requires 3 * depth + ceil(log2(nframes)) <= 64;
- * nframes in [1, 65536]; n < 2^30.  tune NULL = autotuned (see below) or
- * default digit width and tile size; results never depend on it. */
+ * nframes in [1, 65536]; n < 2^30.  tune NULL = buckets where they are faster,
+ * else the autotuned (see below) or default digit width and tile size of the
+ * sort; results never depend on it. */
 size_t cga_batch_workspace_bytes(const cga_grid *grid, int nframes, int64_t n);
 /* Key bits the batched sort's passes cover for nframes frames on this grid
  * (3*depth when segmented, else 3*depth + ceil(log2(nframes))): the
@@ -469,7 +471,8 @@ int cga_batch_graph_destroy(void *graph);
  * keys of key_bytes width and key_bits significant bits -- a copy of d_keys,
  * or synthetic hashed keys when d_keys is NULL -- and records the fastest for
  * (key_bytes, key_bits, floor(log2 n)).  Later calls with tune == NULL
- * (build, project, batched) use a recorded choice when one matches.  When
+ * (build, project, batched) that take a radix sort use a recorded choice when
+ * one matches; whether they take one does not depend on it.  When
  * the environment variable CGA_TUNE_CACHE names a file, recorded choices are
  * loaded from it on first use and appended to it.  Returns the choice and its
  * best time in milliseconds. */

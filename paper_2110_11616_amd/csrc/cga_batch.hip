@@ -324,8 +324,8 @@ static int batch_sort_bits(const cga_grid *g, int F) {
     return 3 * (int)g->depth + (batch_segmented(F) ? 0 : frame_bits_of(F));
 }
 
-// Whether the frames are built by buckets (cga_batch_bucket.h) where no sort was
-// chosen: from four radix passes on, as for a single build, and frames of 2^17 to
+// Whether the frames are built by buckets (cga_batch_bucket.h) where the caller
+// chose no sort: from four radix passes on, as for a single build, and frames of 2^17 to
 // 2^22 points on average, above 42 key bits 3 * 2^20 (us of the radix passes
 // against buckets, LiDAR sweeps of 36-bit keys: 64 frames of 8.5k 145 / 179, 8 of
 // 66k 143 / 169, 12 of 788k 505 / 419, 256 of 10k to 2M 4081 / 3088; surfaces in
@@ -604,8 +604,7 @@ int cga_batch_build_merge(const cga_grid *g, const float *d_xyz, const int64_t *
     BatchArgs a{*g, d_xyz, d_off, nframes, n, d_keys, d_counts, d_key_off, d_merged, d_merged_off,
                 d_merged_cnt, d_ws, ws_bytes, SortCfg()};
     CGA_TRY(resolve_cfg(tune, 8, batch_sort_bits(g, nframes), n, &a.cfg));
-    a.buckets = !tune && batch_buckets(g, nframes, n) &&
-                !tuned_sort_cfg(8, batch_sort_bits(g, nframes), n, &a.cfg);
+    a.buckets = !tune && batch_buckets(g, nframes, n);
     return batch_run(a, (hipStream_t)stream);
 }
 
@@ -621,8 +620,7 @@ int cga_batch_graph_create(const cga_grid *g, const float *d_xyz, const int64_t 
     BatchArgs a{*g, d_xyz, d_off, nframes, n, d_keys, d_counts, d_key_off, d_merged, d_merged_off,
                 d_merged_cnt, d_ws, ws_bytes, SortCfg()};
     CGA_TRY(resolve_cfg(tune, 8, batch_sort_bits(g, nframes), n, &a.cfg));
-    a.buckets = !tune && batch_buckets(g, nframes, n) &&
-                !tuned_sort_cfg(8, batch_sort_bits(g, nframes), n, &a.cfg);
+    a.buckets = !tune && batch_buckets(g, nframes, n);
     if (ws_bytes < batch_layout(nullptr, g, nframes, n, a.cfg).bytes) return CGA_EWORKSPACE;
     persistent_groups();  // query the device before capture
     hipStream_t cs;

@@ -169,7 +169,8 @@ static void build_enqueue(const cga_grid *g, const float *xyz, int64_t n, K *key
 }
 
 // Whether a build goes by buckets (cga_bucket.h) rather than by a sort of all
-// keys, where neither the caller nor the tuning cache chose a sort.  Three
+// keys, where the caller chose no sort.  (The autotuner times sorts alone: its
+// record says which sort is best where one is taken.)  Three
 // 8-bit passes are no dearer than the buckets (24-bit keys, 20k to 1M points:
 // 42 to 84 us against 44 to 81), from four on the buckets win (us of a sort
 // against buckets: 30-bit keys 20k 50 / 44, 1M 101 / 87, 7M 283 / 244; 36-bit
@@ -322,8 +323,7 @@ int cga_build(const cga_grid *g, const float *d_xyz, int64_t n, void *d_keys, ui
     hipStream_t s = (hipStream_t)stream;
     BuildLayout L = build_layout(d_ws, g, n, cfg);
     if (ws_bytes < L.bytes) return CGA_EWORKSPACE;
-    if (bucket_build(g, n) && !tune &&
-        !tuned_sort_cfg(wide ? 8 : 4, 3 * (int)g->depth, n, &cfg)) {
+    if (bucket_build(g, n) && !tune) {
         const BucketLayout B = bucket_layout(d_ws, g, n);
         if (ws_bytes >= B.bytes) {
             int64_t *out = d_n_out ? d_n_out : &B.ctl->count;

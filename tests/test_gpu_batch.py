@@ -247,3 +247,32 @@ def test_autotuner_choice_is_used_and_exact(gpu, frames):
     k, c = gpu.cga_build(dev(frames["xyz"]), g)  # picks the recorded choice
     wk, wc = oracle.build(frames["xyz"], g)
     assert np.array_equal(u64(k), wk) and np.array_equal(u32(c), wc)
+
+
+def test_autotuner_keeps_the_buckets(gpu):
+    """A recorded sort is for calls that sort: builds and batches that go by
+    buckets still do, and one that names a sort gets it."""
+    g = gen.Grid((0.0, 0.0, 0.0), 2.0 ** 12, 12, gen.KEY_MORTON)
+    n = 600_000
+    gpu.cga_autotune_sort(key_bytes=8, key_bits=36, n=n)
+    p = torch.rand((n, 3), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda")
+    off = dev(np.array([0, 250_000, n], np.int64))
+    outs = []
+    for tune, call in ((None, lambda t: gpu.cga_build(p, g, tune=t)),
+                       ((8, 16), lambda t: gpu.cga_build(p, g, tune=t)),
+                       (None, lambda t: gpu.cga_batch_build_merge(p, off, g, tune=t)),
+                       ((8, 16), lambda t: gpu.cga_batch_build_merge(p, off, g, tune=t))):
+        gpu.cga_prof_enable(["bucket_sort", "onesweep"])
+        gpu.cga_prof_reset()
+        try:
+            outs.append(call(tune))
+            torch.cuda.synchronize()
+            launches = [gpu.cga_prof_read(x)[1] > 0 for x in ("bucket_sort", "onesweep")]
+        finally:
+            gpu.cga_prof_disable()
+            gpu.cga_prof_reset()
+        assert launches == [tune is None, tune is not None], tune
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    u = int(outs[2].key_off[-1])
+    assert torch.equal(outs[2].key_off, outs[3].key_off)
+    assert torch.equal(outs[2].keys[:u], outs[3].keys[:u])
