@@ -366,6 +366,17 @@ def by_buckets(pipe):
             and all((1 << 13) <= n <= top for n in (pipe.na, pipe.nb)))
 
 
+def by_tiles(pipe):
+    """Whether the library projects this workload's union by pixel tiles
+    (restated here for the report): MORTON keys up to depth 14, 64 voxels to a
+    tile on average and no sort chosen by the caller.  The sort that follows
+    the tiles in the stream then has nothing to do."""
+    d = pipe.g.depth
+    level = min(d, max(4, min(7, d - 6)))
+    return (pipe.tune_proj is None and pipe.g.key_mode == 0 and d <= 14
+            and pipe.nm >= 64 * 4 ** (d - level))
+
+
 def algorithmic_bytes(label, pipe, counts, build_merge_only=False, rb=(8, 8)):
     """Bytes the method itself must move for a kernel label over one step
     (reads + writes of its essential inputs and outputs); build_merge_only
@@ -377,8 +388,9 @@ def algorithmic_bytes(label, pipe, counts, build_merge_only=False, rb=(8, 8)):
     passes2 = sort_passes(2 * pipe.g.depth, rb[1])
     ua, ub, um = counts[:3]
     ups = counts[3:] if not build_merge_only else []
+    buckets, tiles = by_buckets(pipe), by_tiles(pipe)
     nproj = len(ups)
-    buckets = by_buckets(pipe)
+    nsorted = 0 if tiles else nproj
     if label == "bucket_sort":
         # every key read, every run's value and length written
         return kb * (pipe.na + pipe.nb) + (kb + 4) * (ua + ub) if buckets else None
@@ -390,18 +402,22 @@ def algorithmic_bytes(label, pipe, counts, build_merge_only=False, rb=(8, 8)):
     if label == "onesweep":
         # every pass reads and writes each key once
         return ((0 if buckets else passes3 * 2 * kb * (pipe.na + pipe.nb))
-                + nproj * passes2 * 2 * k2b * um)
+                + nsorted * passes2 * 2 * k2b * um)
     if label == "encode":
         return (12 + kb + (2 if buckets else 0)) * (pipe.na + pipe.nb)
     if label == "rle":
         return ((0 if buckets else kb * (pipe.na + pipe.nb) + (kb + 4) * (ua + ub))
-                + sum(k2b * um + (k2b + 4) * up for up in ups))
+                + sum(k2b * um + (k2b + 4) * up for up in ups[:nsorted]))
     if label == "merge":
         return kb * (ua + ub + um)
     if build_merge_only:
         return None
     if label == "rekey":
-        return nproj * (kb + k2b) * um
+        # every key read, for the runs of its cells or to its pixel key
+        return nproj * (kb + (0 if tiles else k2b)) * um
+    if label == "project_tiles":
+        # every key read, every pixel written by its tile, read and put in place
+        return sum(kb * um + (4 + 4 + k2b + 4) * up for up in ups) if tiles else None
     if label == "knn_tree":
         # read every key of the union once
         return kb * um
@@ -839,12 +855,13 @@ def attribute_values(cga, pipe, d, reps=20):
 
 def c4_batched(cga, device, reps):
     """256 LiDAR frames (log-uniform 10k..2M points) built and pair-merged by
-    one replay of the captured graph; the sort's digit width and tile size
-    come from the autotuner run on the same number of keys.  Roofline: the
-    method's bytes for every frame's build (quantize + encode, the autotuned
-    number of sort passes over the key bits the frame-segmented sort covers,
-    run-length compaction)
-    and every pair's merge, over the replay time."""
+    one replay of the captured graph, by buckets or, where the library takes
+    the sort, with the digit width and tile size of the autotuner run on the
+    same number of keys.  Roofline: the method's bytes for every frame's build
+    (quantize + encode, then the scatter to buckets, their sort and their runs'
+    way to the output, or the autotuned number of sort passes over the key bits
+    the frame-segmented sort covers and run-length compaction) and every pair's
+    merge, over the replay time."""
     import numpy as np
     import torch
 
@@ -878,12 +895,12 @@ def c4_batched(cga, device, reps):
     ms = float(np.median([a.elapsed_time(b) for a, b in ev]))
     # per-kernel times of the same work launched eagerly (HIP events around
     # each launch; the graph itself cannot carry them)
-    labels = ["batch_encode", "hist_scan", "onesweep", "rle", "batch_offsets", "batch_pairs",
-              "batch_merge"]
+    labels = ["bucket_sample", "batch_encode", "bucket_scatter", "bucket_sort", "bucket_emit",
+              "hist_scan", "onesweep", "rle", "batch_offsets", "batch_pairs", "batch_merge"]
     cga.cga_prof_reset()
     cga.cga_prof_enable(labels)
     for _ in range(2):
-        cga.cga_batch_build_merge(xyz, off, g, tune=(rb, items))
+        cga.cga_batch_build_merge(xyz, off, g)
     torch.cuda.synchronize()
     cga.cga_prof_disable()
     kern = {}
@@ -904,7 +921,11 @@ def c4_batched(cga, device, reps):
     merged = int(mc.sum())
     graph.close()
     S, P = 8, sort_passes(key_bits, rb)
-    build_bytes = n * (12 + S + 2 * S * P + S) + u * (S + 4)
+    if "bucket_sort" in kern:
+        # encode, scatter, sort and emit, as in algorithmic_bytes
+        build_bytes = n * (12 + S + 2) + n * (2 * S + 2) + n * S + 3 * u * (S + 4)
+    else:
+        build_bytes = n * (12 + S + 2 * S * P + S) + u * (S + 4)
     merge_bytes = S * int((uf[:-1] + uf[1:]).sum() + merged)
     total = build_bytes + merge_bytes
     gbs = total / (ms * 1e-3) / 1e9
@@ -935,7 +956,7 @@ def main():
     if args.only == "c4":
         # the 256-frame batched graph alone, replayed `steps` times
         c4 = c4_batched(cga, device, args.steps)
-        progress(f"c4 only: graph {c4['graph_ms']} ms, onesweep {c4['kernels_eager'].get('onesweep')}")
+        progress(f"c4 only: graph {c4['graph_ms']} ms, {c4['kernels_eager']}")
         return
     wl_label, drops = WORKLOADS[args.workload]
     progress(f"generating workload {args.workload}")
@@ -997,7 +1018,7 @@ def main():
     # per-kernel breakdown (untimed serial steps)
     labels = ["begin", "bucket_sample", "encode", "bucket_scatter", "bucket_sort", "bucket_emit",
               "histogram", "hist_scan", "onesweep", "rle", "merge_partition",
-              "merge", "rekey", "knn_order", "knn_tree", "knn", "index_root", "index_bounds",
+              "merge", "rekey", "project_tiles", "knn_order", "knn_tree", "knn", "index_root", "index_bounds",
               "index_fit", "index_err", "index_lookup", "binary_lookup"]
     kern_ms = {}
     if not args.no_kernel_timing:
@@ -1122,7 +1143,7 @@ def main():
         algo = algorithmic_bytes(lb, pipe, counts, rb=rbs)
         if lb == "knn":
             algo = nq * knn_bytes_q
-        if algo is None or kms <= 0:
+        if not algo or kms <= 0:  # None: not restated here; 0: launches with nothing to do
             continue
         gbs = algo / (kms * 1e-3) / 1e9
         by_kernel[lb] = {"ms_per_step": kms, "algorithmic_mb_per_step": round(algo / 1e6, 2),
