@@ -487,8 +487,13 @@ int cga_autotune_sort(const void *d_keys, uint32_t key_bytes, uint32_t key_bits,
  * "" = every kernel) is bracketed by two HIP events on the launch's own
  * stream.  cga_prof_read waits for all pending events and returns the summed
  * duration and launch count of one label since the last reset.  Labels:
- * begin, encode, histogram, hist_scan, onesweep, rle, arrays,
- * merge_partition, merge, rekey, knn, binary_lookup.  Not for graph capture. */
+ * begin, encode, histogram, hist_scan, onesweep, onesweep_kv, rle,
+ * bucket_sample, bucket_scatter, bucket_sort, bucket_emit, arrays,
+ * arrays_lookup, arrays_nn, merge_partition, merge, rekey, project_tiles,
+ * occupancy, knn_order, knn_rekey, knn_tree, knn, knn_count, binary_lookup,
+ * temporal_kmeans, temporal_match, batch_encode, batch_offsets, batch_pairs,
+ * batch_merge, stream_probe, and those of the values and the learned index.
+ * Not for graph capture. */
 int cga_prof_enable(const char *filter);
 int cga_prof_disable(void);
 int cga_prof_reset(void);

@@ -107,8 +107,9 @@ inline void bk_carve(Carve &c, BkWs &w, int64_t n, size_t kb) {
 }
 
 // ---------------------------------------------------------------- sample
-// Position of sample i of S over n points: hashed within its stretch, so that
-// no regularity of the input meets the sampling.
+// Position of sample i of S over n points: hashed within its stretch (the mix is
+// MurmurHash3's 32-bit finalizer, in the public domain), so that no regularity
+// of the input meets the sampling.
 __device__ __forceinline__ int64_t bk_sample_at(int64_t i, int64_t S, int64_t n, uint32_t seed) {
     const int64_t lo = i * n / S, hi = (i + 1) * n / S;
     uint32_t h = (uint32_t)i * 0x9E3779B9u + seed;

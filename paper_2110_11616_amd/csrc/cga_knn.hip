@@ -728,7 +728,8 @@ struct PackedList {
     static constexpr bool kBatch = E == 1;
     static constexpr int kBatchMin = 4;  // offers of one team from which the batch is used
     // Offers below 2^28 whose order by index is that of their lanes (a leaf's
-    // voxels, from index `first` on) are sorted as distance << 4 | lane.
+    // voxels, from index `first` on) are sorted as distance << 4 | lane.  None
+    // of them reads as "nothing": 2^28 - 1 is 7 mod 8, no sum of three squares.
     __device__ __forceinline__ void insert_leaf(uint32_t d, bool offered, uint32_t first, int tl) {
         uint32_t v = offered ? (d << 4) | (uint32_t)tl : ~0u;
         const bool b0 = tl & 1, b1 = tl & 2, b2 = tl & 4, b3 = tl & 8;
