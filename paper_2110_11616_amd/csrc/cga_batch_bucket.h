@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kBkBlock) void k_bb_encode(const float *__restrict_
                                                         K *__restrict__ keys,
                                                         uint16_t *__restrict__ ids, uint32_t *gbin,
                                                         uint32_t *err) {
-    __shared__ K s_split[kBbMax];
+    __shared__ K s_tree[kBbMax];
     __shared__ uint32_t s_bin[2 * kBbMax];
     int64_t c0 = (int64_t)blockIdx.x * chunk;
     const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
@@ -147,11 +147,10 @@ __global__ __launch_bounds__(kBkBlock) void k_bb_encode(const float *__restrict_
         const int b0 = fb[f], nb = fb[f + 1] - b0;
         int p2 = 1;
         while (p2 < nb) p2 <<= 1;
-        for (int i = threadIdx.x; i < p2; i += kBkBlock)
-            s_split[i] = i < nb - 1 ? split[b0 + i] : ~K(0);
+        bk_load_tree(split + b0, nb - 1, p2, s_tree);
         for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) s_bin[i] = 0;
         __syncthreads();
-        bad |= bk_encode_range<K>(xyz, c0, e, g, s_split, p2, keys, ids, s_bin);
+        bad |= bk_encode_range<K>(xyz, c0, e, g, s_tree, p2, keys, ids, s_bin);
         __syncthreads();
         uint32_t *out = gbin + ((size_t)(blockIdx.x % kBkXcds) * nb_all + b0) * 2;
         for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) {

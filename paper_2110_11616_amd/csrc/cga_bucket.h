@@ -243,12 +243,23 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_group_rank(const uint32_t *__re
 // ---------------------------------------------------------------- encode
 constexpr int kBkUnroll = 4;
 
-// Points [c0, c1) to keys and bins, the bins' counts to s_bin; s_split holds the
-// splitters padded with the largest value to p2, a power of two.  Returns
-// whether a coordinate is not finite.
+// The splitters in LDS: a search tree level by level (node j's children 2 j and
+// 2 j + 1, the root 1), padded with the largest value to p2 - 1, p2 a power of
+// two.  In ascending order all probes of a search step lay a power of two apart,
+// in one bank: the encode of 10M points stalled for 60 of its 88 us on that.
+template <typename K>
+__device__ __forceinline__ void bk_load_tree(const K *__restrict__ split, int m, int p2, K *s_tree) {
+    for (int i = 1 + (int)threadIdx.x; i < p2; i += kBkBlock) {  // i - 1 splitters below it
+        const int t = __ffs(i);
+        s_tree[(p2 >> t) + (i >> t)] = i <= m ? split[i - 1] : ~K(0);
+    }
+}
+
+// Points [c0, c1) to keys and bins, the bins' counts to s_bin.  Returns whether a
+// coordinate is not finite.
 template <typename K>
 __device__ __forceinline__ bool bk_encode_range(const float *__restrict__ xyz, int64_t c0, int64_t c1,
-                                                const BkGrid &g, const K *s_split, int p2,
+                                                const BkGrid &g, const K *s_tree, int p2,
                                                 K *__restrict__ keys, uint16_t *__restrict__ ids,
                                                 uint32_t *s_bin) {
     const float o[3] = {g.o0, g.o1, g.o2};
@@ -269,18 +280,20 @@ __device__ __forceinline__ bool bk_encode_range(const float *__restrict__ xyz, i
             const bool ok = quantize3(p[u][0], p[u][1], p[u][2], o, g.scale, g.depth, v);
             bad |= !ok && i0 + u * kBkBlock < c1;
             k[u] = (K)enc3(v.x, v.y, v.z, g.depth, g.linear != 0);
-            at[u] = 0;
+            at[u] = 1;
         }
         for (int h = p2 >> 1; h; h >>= 1) {
 #pragma unroll
-            for (int u = 0; u < kBkUnroll; ++u)
-                at[u] += s_split[at[u] + h - 1] < k[u] ? h : 0;
+            for (int u = 0; u < kBkUnroll; ++u) at[u] = 2 * at[u] + (s_tree[at[u]] < k[u] ? 1 : 0);
         }
 #pragma unroll
         for (int u = 0; u < kBkUnroll; ++u) {
             const int64_t i = i0 + u * kBkBlock;
             if (i >= c1) continue;
-            const uint32_t id = 2 * at[u] + (s_split[at[u]] == k[u] ? 1 : 0);
+            // the path ends at leaf p2 + (splitters below the key); the last
+            // node that it left downwards is the next splitter (0: there is none)
+            const int next = at[u] >> __ffs(~at[u]);
+            const uint32_t id = 2 * (at[u] - p2) + (next && s_tree[next] == k[u] ? 1 : 0);
             keys[i] = k[u];
             ids[i] = (uint16_t)id;
             // neighbouring points mostly share a bin: one add for all of them
@@ -306,14 +319,14 @@ __global__ __launch_bounds__(kBkBlock) void k_bk_encode(const float *__restrict_
                                                         uint16_t *__restrict__ ids, uint32_t *gbin,
                                                         uint32_t *err) {
     extern __shared__ uint64_t s_dyn[];
-    K *s_split = (K *)s_dyn;                       // p2
-    uint32_t *s_bin = (uint32_t *)(s_split + p2);  // 2 nb
-    for (int i = threadIdx.x; i < p2; i += kBkBlock) s_split[i] = i < nb - 1 ? split[i] : ~K(0);
+    K *s_tree = (K *)s_dyn;                       // p2
+    uint32_t *s_bin = (uint32_t *)(s_tree + p2);  // 2 nb
+    bk_load_tree(split, nb - 1, p2, s_tree);
     for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) s_bin[i] = 0;
     __syncthreads();
     const int64_t c0 = (int64_t)blockIdx.x * chunk;
     const int64_t c1 = c0 + chunk < n ? c0 + chunk : n;
-    if (bk_encode_range<K>(xyz, c0, c1, g, s_split, p2, keys, ids, s_bin))
+    if (bk_encode_range<K>(xyz, c0, c1, g, s_tree, p2, keys, ids, s_bin))
         set_err(err, ERR_NONFINITE);
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * nb; i += kBkBlock) {

@@ -193,6 +193,24 @@ def test_build_bucket_ends(gpu, n, depth, mode, buckets):
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+@pytest.mark.parametrize("n", [8_193, 16_384, 16_385, 65_536, 65_537, 524_288, 1 << 22, (1 << 22) + 1])
+@pytest.mark.parametrize("kind", ["uniform", "repeated"])
+def test_build_bucket_trees(gpu, n, kind):
+    """Bucket counts at and next to powers of two, where the splitters' tree is
+    full or has one more level: keys below the first splitter, above the last,
+    equal to one, and splitters that repeat."""
+    rng = torch.Generator(device="cuda").manual_seed(n)
+    p = torch.rand((n, 3), generator=rng, device="cuda")
+    if kind == "repeated":
+        p = p[torch.randint(0, 5000, (n,), generator=rng, device="cuda")].contiguous()
+        p[:3] = torch.tensor([[0.0] * 3, [1.0] * 3, [0.5] * 3], device="cuda")
+    for mode in (M, L):
+        g = Grid((0.0, 0.0, 0.0), 2.0 ** 13, 13, mode)
+        k, c = gpu.cga_build(p, g)
+        wk, wc = gpu.cga_build(p, g, tune=(8, 16))
+        assert torch.equal(k, wk) and torch.equal(c, wc)
+
+
 @pytest.mark.parametrize("wl", ["w_c1", "w_c2s", "w_c3s"])
 @pytest.mark.parametrize("mode", [M, L])
 def test_build(gpu, wl, mode, request):
