@@ -358,12 +358,10 @@ def library_sort_default(key_bytes, key_bits, n):
 
 def by_buckets(pipe):
     """Whether the library builds this workload's clouds by buckets (restated
-    here for the report): more than 24 key bits, 2^13 to 10 * 2^20 points (2^23
-    with 32-bit keys) and no sort chosen by the caller."""
-    bits = 3 * pipe.g.depth
-    top = 10 << 20 if bits > 32 else 1 << 23
-    return (pipe.tune_build is None and bits > 24
-            and all((1 << 13) <= n <= top for n in (pipe.na, pipe.nb)))
+    here for the report): more than 24 key bits, 2^13 to 12 * 2^20 points and no
+    sort chosen by the caller."""
+    return (pipe.tune_build is None and 3 * pipe.g.depth > 24
+            and all((1 << 13) <= n <= 12 << 20 for n in (pipe.na, pipe.nb)))
 
 
 def by_tiles(pipe):

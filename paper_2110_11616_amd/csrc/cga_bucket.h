@@ -16,17 +16,18 @@
 //      through global memory by its block, slowly.  With eight samples a bucket
 //      (at hashed positions, repeated keys made splitters) one of 4096 keys on
 //      average is over kBkCap with probability 3e-7, over the half with 3 %:
-//      2M to 10M points of wide spans (a filled volume, or a surface of 14 bits
+//      2M to 12M points of wide spans (a filled volume, or a surface of 14 bits
 //      an axis and more in random order) have some tens of those and still gain
 //      (filled volume of 63-bit keys, us of a sort against buckets: 2M 262 / 217,
 //      4M 406 / 305, 8M 583 / 507).
 //   6. emit: the buckets' runs to their places in the output.
-// Measured, 10M points of a surface in random order, 42-bit keys: sample 31 us,
-// encode 88, scan 7, scatter 94 (1.9 TB/s; 128 with a range per block instead of
-// the shared cursors), sort 157 (LDS and barriers; 392 with a look-back for the
-// place of its output), emit 54 (4.4 TB/s): 431 against 515 of six radix passes
-// and a compaction (kernel times; the calls take 474 and 514).  1M LiDAR points,
-// 36 bits: 84 against 126.
+// Measured, 10M points of a surface in random order, 42-bit keys (us): sample 31,
+// encode 60, scan 7, scatter 96 (1.9 TB/s by its own bytes, but it writes 3.6 times
+// those in lines that leave part-filled; 128 with a range per block instead of the
+// shared cursors), sort 158 (LDS and barriers: its waves wait 59 % of their time;
+// 392 with a look-back for the place of its output), emit 55 (4.4 TB/s); the call
+// 447 against 514 by six radix passes and a compaction.  1M LiDAR points, 36 bits:
+// 84 against 126.
 #pragma once
 
 #include "cga_common.h"
@@ -246,7 +247,8 @@ constexpr int kBkUnroll = 4;
 // The splitters in LDS: a search tree level by level (node j's children 2 j and
 // 2 j + 1, the root 1), padded with the largest value to p2 - 1, p2 a power of
 // two.  In ascending order all probes of a search step lay a power of two apart,
-// in one bank: the encode of 10M points stalled for 60 of its 88 us on that.
+// in one bank: so the encode of 10M points took 88 us, 60 of them conflicts, and
+// takes 60.
 template <typename K>
 __device__ __forceinline__ void bk_load_tree(const K *__restrict__ split, int m, int p2, K *s_tree) {
     for (int i = 1 + (int)threadIdx.x; i < p2; i += kBkBlock) {  // i - 1 splitters below it

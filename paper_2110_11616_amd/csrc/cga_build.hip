@@ -170,21 +170,20 @@ static void build_enqueue(const cga_grid *g, const float *xyz, int64_t n, K *key
 
 // Whether a build goes by buckets (cga_bucket.h) rather than by a sort of all
 // keys, where the caller chose no sort.  (The autotuner times sorts alone: its
-// record says which sort is best where one is taken.)  Three
-// 8-bit passes are no dearer than the buckets (24-bit keys, 20k to 1M points:
-// 42 to 84 us against 44 to 81), from four on the buckets win (us of a sort
-// against buckets: 30-bit keys 20k 50 / 44, 1M 101 / 87, 7M 283 / 244; 36-bit
-// 1M 125 / 90, 5M 303 / 183; 48-bit 1M 145 / 93, 10M 538 / 366) until the points
-// in random order are so many that the partition writes scattered lines: 32-bit
-// keys 8M 294 / 270, 10M 343 / 375; wider ones 10M 538 / 540 at 48 bits and 514 /
-// 474 at 42, 12M 608 / 637 and 580 / 574, 16M 763 / 825 and 727 / 755 (LiDAR
-// sweeps, in order, would gain on: 16M 736 / 523 at 42 bits).  Below some thousand
-// points the extra launches show (4096 points 44 / 49).
-constexpr int64_t kBucketLeast = 1 << 13, kBucketMost32 = 1 << 23, kBucketMost = 10 << 20;
+// record says which sort is best where one is taken.)  Three 8-bit passes are no
+// dearer than the buckets (24-bit keys, 20k to 1M points: 42 to 84 us against 44
+// to 81), from four on the buckets win (us of a sort against buckets: 30-bit keys
+// 20k 50 / 44, 1M 101 / 87, 7M 278 / 228; 36-bit 1M 125 / 90, 4M 277 / 188; 48-bit
+// 1M 145 / 93, 10M 537 / 511) until the points in random order are so many that
+// the partition writes scattered lines (surface: 12.5M points 30-bit 388 / 354,
+// 42-bit 599 / 522, 48-bit 627 / 623, 15M 448 / 461, 695 / 702, 723 / 783; filled
+// volume: 12.5M of 48 bits 633 / 614, 13M 651 / 684; LiDAR sweeps, in order, would
+// gain on: 15M of 42 bits 699 / 484).  Below some thousand points the extra launches
+// show (4096 points 44 / 49).
+constexpr int64_t kBucketLeast = 1 << 13, kBucketMost = 12 << 20;
 
 static bool bucket_build(const cga_grid *g, int64_t n) {
-    const int bits = 3 * (int)g->depth;
-    return bits > 24 && n >= kBucketLeast && n <= (bits > 32 ? kBucketMost : kBucketMost32);
+    return 3 * (int)g->depth > 24 && n >= kBucketLeast && n <= kBucketMost;
 }
 
 struct BucketLayout {

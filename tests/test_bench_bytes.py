@@ -39,7 +39,7 @@ def test_projections_by_the_sort_are_billed(kw):
 
 
 def test_builds_by_the_sort_are_billed():
-    p = _pipe(n=11_000_000)  # above the bucket rule's end
+    p = _pipe(n=13_000_000)  # above the bucket rule's end
     assert bench.algorithmic_bytes("bucket_sort", p, COUNTS) is None
     passes = -(-42 // 8)
-    assert bench.algorithmic_bytes("onesweep", p, COUNTS) == passes * 16 * 22_000_000
+    assert bench.algorithmic_bytes("onesweep", p, COUNTS) == passes * 16 * 26_000_000

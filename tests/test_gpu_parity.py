@@ -174,8 +174,8 @@ def _routes(gpu, labels, call):
 
 @pytest.mark.parametrize("n,depth,mode,buckets", [
     ((1 << 13) - 1, 12, M, False), (1 << 13, 12, L, True), (100_000, 8, M, False),
-    (1 << 23, 10, M, True), ((1 << 23) + 1, 10, M, False),
-    (10 << 20, 12, L, True), (10 << 20, 16, M, True), ((10 << 20) + 1, 16, M, False),
+    (12 << 20, 10, M, True), ((12 << 20) + 1, 10, M, False),
+    (12 << 20, 12, L, True), (12 << 20, 16, M, True), ((12 << 20) + 1, 16, M, False),
     (5_000_001, 21, M, True), (5_000_001, 21, L, True)])
 def test_build_bucket_ends(gpu, n, depth, mode, buckets):
     """Which builds go by buckets, at the rule's ends and with millions of wide
